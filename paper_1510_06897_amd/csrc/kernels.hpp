@@ -6,6 +6,8 @@
 // one pass over memory (the kernel merging the paper credits with its largest gain, Sec. 2).
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 #include "stencil.hpp"
 
@@ -935,83 +937,167 @@ __global__ void __launch_bounds__(kBlock)
   }
 }
 
-// Deflation projection on the matrix cores (FP32 storage): c[r][e] = sum_k conj(phi_e[k]) psi_r[k]
-// as a real product C = A B with K = 24 V reals (complex numbers stored as (re, im) pairs):
+// Deflation projection on the matrix cores: c[r][e] = sum_k conj(phi_e[k]) psi_r[k] as a real
+// product C = A B with K = 24 V reals (complex numbers stored as (re, im) pairs):
 //   A[e][k] = raw phi_e data,  B[k][2r] = raw psi_r data,  B[k][2r+1] = psi_r pairs (re, im)
 //   turned into (im, -re),  so C[e][2r] = Re c and C[e][2r+1] = Im c.
-// One wave accumulates a 16 x 16 tile (16 eigenvectors x 8 right-hand sides) with
-// v_mfma_f32_16x16x4f32 over its share of K (lane l holds A[l % 16][k0 + l / 16] and
-// B[k0 + l / 16][l % 16]; each lane reads MT consecutive reals per step); the four waves of a
-// workgroup are added in FP64 in fixed order and pass 2 sums the workgroups in FP64.
+// One wave accumulates TE x TR tiles of 16 eigenvectors x 8 right-hand sides over its share of K
+// (lane l holds A[l % 16][k0 + l / 16] and B[k0 + l / 16][l % 16]; each lane reads kMfmaT
+// consecutive reals per step), so one pass over memory serves up to 32 vectors and 16 right-hand
+// sides.  FP32 data: v_mfma_f32_16x16x4f32, each step's FP32 sums added into FP64 registers.  FP64
+// data: v_mfma_f64_16x16x4f64, FP64 throughout.  The four waves of a workgroup are added in FP64 in
+// fixed order and pass 2 sums the workgroups in FP64.
+// Bound by memory: the bytes are the basis and the right-hand sides once each (24 FP64 vectors and 12
+// right-hand sides of 16^3 x 32: 906 MB in 221 us, 4.1 TB/s; the VALU kernel, which reads the basis
+// once per right-hand side, takes 1.35 ms).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaT = 4;  // reals per lane per step
 
+// kMfmaT consecutive reals of one vector.  FP32 operands are read through a buffer resource over the
+// whole block (its offsets are 32-bit: the host checks the span), FP64 ones by 64-bit address.
+struct MfmaSrc {
+  rsrc_t r;
+  const double *p;
+};
+template <class SE>
+__device__ __forceinline__ void mfma_load(const MfmaSrc &m, int row, int64_t K, int64_t k,
+                                          typename std::conditional<sizeof(SE) == 8, float, double>::type v[kMfmaT]) {
+  if constexpr (sizeof(SE) == 8) {
+    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(m.r, (uint32_t)row * (uint32_t)(K * 4) + (uint32_t)k * 4u, 0u, 0);
+    v[0] = __uint_as_float(w.x);
+    v[1] = __uint_as_float(w.y);
+    v[2] = __uint_as_float(w.z);
+    v[3] = __uint_as_float(w.w);
+  } else {
+    const double2 *q = reinterpret_cast<const double2 *>(m.p + (int64_t)row * K + k);
+    const double2 x = q[0], y = q[1];
+    v[0] = x.x;
+    v[1] = x.y;
+    v[2] = y.x;
+    v[3] = y.y;
+  }
+}
+
+template <class SE, int TE, int TR>
 __global__ void __launch_bounds__(256)
-    project_mfma_kernel(const float *phi, int n_ev, const float *psi, int nrhs, int psi_g5, int V,
+    project_mfma_kernel(const SE *phi, int n_ev, const SE *psi, int nrhs, int psi_g5, int V,
                         int chunk, double2 *__restrict__ partial) {
+  constexpr bool F32 = sizeof(SE) == 8;
+  using R = typename std::conditional<F32, float, double>::type;
   __shared__ double tile[4][16][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = lane & 15, g = lane >> 4;
-  const int e = blockIdx.y * 16 + i;          // A row of this lane
-  const int col = i;                          // B column of this lane
-  const int r = blockIdx.z * 8 + (col >> 1);  // right-hand side of the column
-  const bool imcol = (col & 1) != 0;
-  const int64_t K = (int64_t)24 * V;          // reals per vector
-  const uint32_t vecb = (uint32_t)K * 4u;     // bytes per vector
-  const rsrc_t ra = make_rsrc(phi, vecb * (uint32_t)n_ev);
-  const rsrc_t rb = make_rsrc(psi, vecb * (uint32_t)nrhs);
-  const bool arow = e < n_ev, bcol = r < nrhs;
+  const int e0 = blockIdx.y * 16 * TE, r0 = blockIdx.z * 8 * TR;
+  const bool imcol = (i & 1) != 0;
+  const int64_t K = (int64_t)24 * V;  // reals per vector
+  MfmaSrc sa, sb;
+  if constexpr (F32) {
+    sa.r = make_rsrc(phi, (uint32_t)(K * 4) * (uint32_t)n_ev);
+    sb.r = make_rsrc(psi, (uint32_t)(K * 4) * (uint32_t)nrhs);
+  } else {
+    sa.p = reinterpret_cast<const double *>(phi);
+    sb.p = reinterpret_cast<const double *>(psi);
+  }
+  // rows of A and columns of B past the data: the last valid vector is read and masked to zero
+  int er[TE], rr[TR];
+  bool arow[TE], bcol[TR];
+#pragma unroll
+  for (int x = 0; x < TE; ++x) {
+    const int e = e0 + 16 * x + i;
+    arow[x] = e < n_ev;
+    er[x] = arow[x] ? e : n_ev - 1;
+  }
+#pragma unroll
+  for (int y = 0; y < TR; ++y) {
+    const int r = r0 + 8 * y + (i >> 1);
+    bcol[y] = r < nrhs;
+    rr[y] = bcol[y] ? r : nrhs - 1;
+  }
   const int64_t k_begin = (int64_t)blockIdx.x * chunk;
   const int64_t k_end = k_begin + chunk < K ? k_begin + chunk : K;
-  // the matrix core accumulates 16 products per lane group in FP32; the running sum is FP64
-  double acc64[4] = {0.0, 0.0, 0.0, 0.0};
-  // Each step covers 4 waves x 4 lane groups x MT reals.  The loop bound is uniform over the wave:
-  // an MFMA reads its operands from every lane regardless of the execution mask, so no lane may
-  // leave the loop early; positions past the chunk are masked to zero instead.
+  double acc64[TE][TR][4];
+#pragma unroll
+  for (int x = 0; x < TE; ++x)
+#pragma unroll
+    for (int y = 0; y < TR; ++y)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc64[x][y][q] = 0.0;
+  // Each step covers 4 waves x 4 lane groups x kMfmaT reals.  The loop bound is uniform over the
+  // wave: an MFMA reads its operands from every lane regardless of the execution mask, so no lane
+  // may leave the loop early; positions past the chunk (a multiple of kMfmaT, like K) read the
+  // vector's start and are masked to zero instead.
   for (int64_t kw = k_begin + (int64_t)wave * 4 * kMfmaT; kw < k_end; kw += 16 * kMfmaT) {
     const int64_t k0 = kw + (int64_t)g * kMfmaT;
-    float a[kMfmaT], bv[kMfmaT];
-    // row offsets differ per lane: they go in the VGPR offset (rows beyond the data read 0)
-    const u32x4 wa = __builtin_amdgcn_raw_buffer_load_b128(ra, (uint32_t)e * vecb + (uint32_t)k0 * 4u, 0u, 0);
-    const u32x4 wb = __builtin_amdgcn_raw_buffer_load_b128(rb, (uint32_t)r * vecb + (uint32_t)k0 * 4u, 0u, 0);
-    a[0] = __uint_as_float(wa.x); a[1] = __uint_as_float(wa.y);
-    a[2] = __uint_as_float(wa.z); a[3] = __uint_as_float(wa.w);
-    float x0 = __uint_as_float(wb.x), y0 = __uint_as_float(wb.y);
-    float x1 = __uint_as_float(wb.z), y1 = __uint_as_float(wb.w);
-    if (psi_g5) {  // gamma5: spin components 2, 3 (complex index >= 6 V) change sign
-      if ((k0 >> 1) >= 6 * (int64_t)V) { x0 = -x0; y0 = -y0; }
-      if (((k0 + 2) >> 1) >= 6 * (int64_t)V) { x1 = -x1; y1 = -y1; }
+    const bool in = k0 < k_end;
+    const int64_t kr = in ? k0 : 0;
+    R a[TE][kMfmaT], b[TR][kMfmaT];
+#pragma unroll
+    for (int x = 0; x < TE; ++x) mfma_load<SE>(sa, er[x], K, kr, a[x]);
+#pragma unroll
+    for (int y = 0; y < TR; ++y) mfma_load<SE>(sb, rr[y], K, kr, b[y]);
+    // gamma5: spin components 2, 3 (reals from 12 V on) change sign
+    const bool n0 = psi_g5 && kr >= (int64_t)12 * V, n1 = psi_g5 && kr + 2 >= (int64_t)12 * V;
+#pragma unroll
+    for (int x = 0; x < TE; ++x)
+#pragma unroll
+      for (int t = 0; t < kMfmaT; ++t) a[x][t] = (in && arow[x]) ? a[x][t] : R(0);
+#pragma unroll
+    for (int y = 0; y < TR; ++y) {
+      const R x0 = n0 ? -b[y][0] : b[y][0], y0 = n0 ? -b[y][1] : b[y][1];
+      const R x1 = n1 ? -b[y][2] : b[y][2], y1 = n1 ? -b[y][3] : b[y][3];
+      const bool keep = in && bcol[y];
+      b[y][0] = keep ? (imcol ? y0 : x0) : R(0);
+      b[y][1] = keep ? (imcol ? -x0 : y0) : R(0);
+      b[y][2] = keep ? (imcol ? y1 : x1) : R(0);
+      b[y][3] = keep ? (imcol ? -x1 : y1) : R(0);
     }
-    if (imcol) { bv[0] = y0; bv[1] = -x0; bv[2] = y1; bv[3] = -x1; }
-    else { bv[0] = x0; bv[1] = y0; bv[2] = x1; bv[3] = y1; }
-    // the lane's A value belongs to row e and its B value to column col: separate masks
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < kMfmaT; ++t) {
-      const bool in = k0 + t < k_end;
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32((in && arow) ? a[t] : 0.f,
-                                                 (in && bcol) ? bv[t] : 0.f, acc, 0, 0, 0);
+    for (int x = 0; x < TE; ++x)
+#pragma unroll
+      for (int y = 0; y < TR; ++y) {
+        // the matrix core sums the step's 16 products per lane group; the running sum is FP64 and
+        // separate (one chain of all the chunk's FP64 products measured 1.6x the rounding error)
+        if constexpr (F32) {
+          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int t = 0; t < kMfmaT; ++t)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[x][t], b[y][t], acc, 0, 0, 0);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc64[x][y][q] += (double)acc[q];
+        } else {
+          f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int t = 0; t < kMfmaT; ++t)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x][t], b[y][t], acc, 0, 0, 0);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) acc64[x][y][q] += acc[q];
+        }
+      }
+  }
+#pragma unroll
+  for (int x = 0; x < TE; ++x)
+#pragma unroll
+    for (int y = 0; y < TR; ++y) {
+      if (x + y > 0) __syncthreads();  // tile[] is reused
+      // lane holds C[row][col = i]: row = 4 g + q (FP32), g + 4 q (FP64), q = 0..3
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        tile[wave][F32 ? 4 * g + q : g + 4 * q][i] = acc64[x][y][q];
+      __syncthreads();
+      if (threadIdx.x < 128) {
+        const int row = threadIdx.x >> 3, c = threadIdx.x & 7;
+        const int ee = e0 + 16 * x + row, rhs = r0 + 8 * y + c;
+        if (ee < n_ev && rhs < nrhs) {
+          double v[2];
+#pragma unroll
+          for (int k = 0; k < 2; ++k)
+            v[k] = tile[0][row][2 * c + k] + tile[1][row][2 * c + k] + tile[2][row][2 * c + k] +
+                   tile[3][row][2 * c + k];
+          partial[((int64_t)blockIdx.x * nrhs + rhs) * n_ev + ee] = make_double2(v[0], v[1]);
+        }
+      }
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc64[q] += (double)acc[q];
-  }
-  // lane holds C[row = 4 g + q][col = i], q = 0..3
-#pragma unroll
-  for (int q = 0; q < 4; ++q) tile[wave][4 * g + q][i] = acc64[q];
-  __syncthreads();
-  if (threadIdx.x < 256) {
-    const int row = threadIdx.x >> 4, c = threadIdx.x & 15;
-    const double sum = tile[0][row][c] + tile[1][row][c] + tile[2][row][c] + tile[3][row][c];
-    tile[0][row][c] = sum;
-  }
-  __syncthreads();
-  if (threadIdx.x < 128) {
-    const int row = threadIdx.x >> 3, rr = threadIdx.x & 7;
-    const int ee = blockIdx.y * 16 + row, rhs = blockIdx.z * 8 + rr;
-    if (ee < n_ev && rhs < nrhs)
-      partial[((int64_t)blockIdx.x * nrhs + rhs) * n_ev + ee] =
-          make_double2(tile[0][row][2 * rr], tile[0][row][2 * rr + 1]);
-  }
 }
 
 // pass 2: c[r][i] = sum_b partial[b][r][i]; one wave per output, lane l sums blocks l, l + 64, ...
@@ -1059,33 +1145,56 @@ __global__ void __launch_bounds__(kBlock)
 }
 
 // inout_r += sum_{e0 <= i < e0 + ne} phi_i (w.v[i - e0] * c[r][i]) with the weights passed by value
-// in the kernel arguments (the public correction entry point: nothing to stage on the device)
-constexpr int kWChunk = 256;
+// in the kernel arguments (the public correction entry point: nothing to stage on the device).
+// A thread owns one spin-colour component of one site for up to RB right-hand sides: every basis
+// element read feeds RB multiply-adds, so the basis is read once per RB right-hand sides; the
+// coefficients w c of the launch sit in LDS.  Bound by memory (24 FP64 vectors added to 12 right-hand
+// sides of 16^3 x 32: 1.21 GB in 272 us, 4.4 TB/s; with the basis read once per right-hand side
+// 1445 us).  Every sum runs over i in ascending order.
+constexpr int kWChunk = 256;  // basis vectors per launch
+constexpr int kWStage = 64;   // of which this many have their coefficients in LDS at a time
 struct WChunk {
   double v[kWChunk];
 };
-template <class C, class SE>
+template <class C, class SE, int RB>
 __global__ void __launch_bounds__(kBlock)
-    correct_w_kernel(SE *inout, const SE *__restrict__ phi, int e0, int ne, int n_ev,
-                     const double2 *__restrict__ c, WChunk w, int V) {
-  const int site = blockIdx.x * kBlock + threadIdx.x;
-  const int r = blockIdx.y;
-  if (site >= V) return;
-  SE *io = inout + (int64_t)r * 12 * V;
-  cx<C> acc[12];
+    correct_w_kernel(SE *inout, const SE *__restrict__ phi, int e0, int ne, int n_ev, int nrhs,
+                     const double2 *__restrict__ c, WChunk w, int64_t n) {
+  __shared__ cx<C> d[kWStage][RB];
+  const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;  // element of a vector, n = 12 V
+  const int r0 = blockIdx.y * RB;
+  const int nr = min(RB, nrhs - r0);
+  const bool in = k < n;
+  SE *io = inout + (int64_t)r0 * n;
+  cx<C> acc[RB];
 #pragma unroll
-  for (int i = 0; i < 12; ++i) acc[i] = load_c<C>(io, (int64_t)i * V + site);
-  for (int k = 0; k < ne; ++k) {
-    const int e = e0 + k;
-    const double2 ce = c[r * n_ev + e];
-    const double we = w.v[k];
-    const cx<C> d = mk<C>(C(ce.x * we), C(ce.y * we));
+  for (int r = 0; r < RB; ++r)
+    if (r < nr && in) acc[r] = load_c<C>(io, (int64_t)r * n + k);
+  for (int s0 = 0; s0 < ne; s0 += kWStage) {
+    const int ns = min(kWStage, ne - s0);
+    __syncthreads();
+    for (int j = threadIdx.x; j < ns * RB; j += kBlock) {
+      const int e = j / RB, r = j % RB;
+      if (r < nr) {
+        const double2 ce = c[(int64_t)(r0 + r) * n_ev + e0 + s0 + e];
+        const double we = w.v[s0 + e];
+        d[e][r] = mk<C>(C(ce.x * we), C(ce.y * we));
+      }
+    }
+    __syncthreads();
+    if (in) {
+#pragma unroll 4
+      for (int e = 0; e < ns; ++e) {
+        const cx<C> f = load_c<C>(phi, (int64_t)(e0 + s0 + e) * n + k);
 #pragma unroll
-    for (int i = 0; i < 12; ++i)
-      acc[i] = cmadd(acc[i], load_c<C>(phi, ((int64_t)e * 12 + i) * V + site), d);
+        for (int r = 0; r < RB; ++r)
+          if (r < nr) acc[r] = cmadd(acc[r], f, d[e][r]);
+      }
+    }
   }
 #pragma unroll
-  for (int i = 0; i < 12; ++i) store_c(io, (int64_t)i * V + site, acc[i]);
+  for (int r = 0; r < RB; ++r)
+    if (r < nr && in) store_c(io, (int64_t)r * n + k, acc[r]);
 }
 
 // v *= 1 / sqrt(nrm2[0].x); records the norm before scaling into norms[slot]

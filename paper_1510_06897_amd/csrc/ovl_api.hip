@@ -512,7 +512,6 @@ StepArgs<false> single_args(const ovl_gauge *g, int nrhs) {
 }
 
 // c[r][i] = phi_i^+ psi_r (FP64 result), scratch `partial` of n_blocks * nrhs * n_ev double2.
-// FP64 storage: VALU kernel with FP64 products; FP32 storage: FP32 matrix-core kernel.
 // workgroups of the two projection kernels; the partial buffer holds project_blocks(V) of either
 int project_blocks_valu(int V) { return std::min(grid_blocks(V), 1024); }
 int project_blocks_mfma(int V) {  // about 1024 reals per workgroup: many short FP32 sums
@@ -520,8 +519,38 @@ int project_blocks_mfma(int V) {  // about 1024 reals per workgroup: many short 
 }
 int project_blocks(int V) { return std::max(project_blocks_valu(V), project_blocks_mfma(V)); }
 
+// Matrix-core projection: tiles of 16 vectors x 8 right-hand sides, up to 2 x 2 per workgroup.
+template <class SE>
+int project_mfma(const SE *phi, int n_ev, const SE *psi, int psi_g5, int nrhs, int V,
+                 double2 *partial, int nblk, double2 *c, hipStream_t s) {
+  const int64_t K = (int64_t)24 * V;
+  nblk = std::min(nblk, project_blocks_mfma(V));
+  // reals per workgroup: a multiple of 64 (4 waves x 4 lane groups x 4 reals)
+  int64_t chunk = (K + nblk - 1) / nblk;
+  chunk = (chunk + 63) / 64 * 64;
+  const int blocks = (int)((K + chunk - 1) / chunk);
+  const int te = n_ev > 16 ? 2 : 1, tr = nrhs > 8 ? 2 : 1;
+  const dim3 grid(blocks, (n_ev + 16 * te - 1) / (16 * te), (nrhs + 8 * tr - 1) / (8 * tr));
+  auto go = [&](auto kernel) {
+    kernel<<<grid, 256, 0, s>>>(phi, n_ev, psi, nrhs, psi_g5, V, (int)chunk, partial);
+  };
+  if (te == 1 && tr == 1) go(project_mfma_kernel<SE, 1, 1>);
+  else if (te == 2 && tr == 1) go(project_mfma_kernel<SE, 2, 1>);
+  else if (te == 1) go(project_mfma_kernel<SE, 1, 2>);
+  else go(project_mfma_kernel<SE, 2, 2>);
+  HIP_TRY(hipGetLastError());
+  const int count = nrhs * n_ev;
+  project_reduce_kernel<<<count, 64, 0, s>>>(partial, blocks, count, c);
+  HIP_TRY(hipGetLastError());
+  return OVL_OK;
+}
+
+// FP64 storage: one right-hand side takes the VALU kernel with FP64 products (each basis vector is
+// read once whatever the kernel); several take the FP64 matrix cores, where one read of the basis
+// serves 16 right-hand sides and one read of a right-hand side 32 vectors.
 int project(const double2 *phi, int n_ev, const double2 *psi, int psi_g5, int nrhs, int V,
             double2 *partial, int nblk, double2 *c, hipStream_t s) {
+  if (nrhs > 1) return project_mfma(phi, n_ev, psi, psi_g5, nrhs, V, partial, nblk, c, s);
   constexpr int CH = 8;
   nblk = std::min(nblk, project_blocks_valu(V));
   dim3 grid(nblk, (n_ev + CH - 1) / CH, nrhs);
@@ -533,24 +562,12 @@ int project(const double2 *phi, int n_ev, const double2 *psi, int psi_g5, int nr
   return OVL_OK;
 }
 
+// FP32 storage: the FP32 matrix cores with FP64 running sums
 int project(const float2 *phi, int n_ev, const float2 *psi, int psi_g5, int nrhs, int V,
             double2 *partial, int nblk, double2 *c, hipStream_t s) {
   if (!fits_u32(12ull * V * nrhs, OVL_F32))
     return fail(OVL_EDIMS, "%d right-hand sides of %d sites exceed 4 GiB", nrhs, V);
-  const int64_t K = (int64_t)24 * V;
-  nblk = std::min(nblk, project_blocks_mfma(V));
-  // reals per workgroup: a multiple of 64 (4 waves x 4 lane groups x 4 reals)
-  int64_t chunk = (K + nblk - 1) / nblk;
-  chunk = (chunk + 63) / 64 * 64;
-  const int blocks = (int)((K + chunk - 1) / chunk);
-  dim3 grid(blocks, (n_ev + 15) / 16, (nrhs + 7) / 8);
-  project_mfma_kernel<<<grid, 256, 0, s>>>((const float *)phi, n_ev, (const float *)psi, nrhs,
-                                           psi_g5, V, (int)chunk, partial);
-  HIP_TRY(hipGetLastError());
-  const int count = nrhs * n_ev;
-  project_reduce_kernel<<<count, 64, 0, s>>>(partial, blocks, count, c);
-  HIP_TRY(hipGetLastError());
-  return OVL_OK;
+  return project_mfma(phi, n_ev, psi, psi_g5, nrhs, V, partial, nblk, c, s);
 }
 
 // Device weights w_i = sign(lambda_i) - p(lambda_i / lmax) (FP64, Sec. 2, eq. 3) of polynomial p
@@ -1983,21 +2000,27 @@ int ovl_defl_correct(const ovl_defl *d, void *inout, const double *c_dev, const 
     if (!std::isfinite(w_host[i])) return fail(OVL_ENONFINITE, "w[%d] is not finite", i);
   hipStream_t s = as_stream(stream);
   const int V = d->g.V;
-  dim3 grid(grid_blocks(V), nrhs);
   // the weights travel in the kernel arguments, kWChunk per launch: nothing is staged on the
   // device and the call returns without waiting
   for (int e0 = 0; e0 < d->n_ev; e0 += kWChunk) {
     const int ne = std::min(kWChunk, d->n_ev - e0);
     WChunk w;
     for (int k = 0; k < kWChunk; ++k) w.v[k] = k < ne ? w_host[e0 + k] : 0.0;
-    if (spin_dt == OVL_F64)
-      correct_w_kernel<double, double2><<<grid, kBlock, 0, s>>>(
-          (double2 *)inout, (const double2 *)d->phi_store, e0, ne, d->n_ev,
-          (const double2 *)c_dev, w, V);
-    else
-      correct_w_kernel<float, float2><<<grid, kBlock, 0, s>>>(
-          (float2 *)inout, (const float2 *)d->phi_store, e0, ne, d->n_ev,
-          (const double2 *)c_dev, w, V);
+    const int64_t n = (int64_t)12 * V;
+    auto go = [&](auto kernel, auto *io, const auto *phi, int rb) {
+      const dim3 grid((unsigned)((n + kBlock - 1) / kBlock), (unsigned)((nrhs + rb - 1) / rb));
+      kernel<<<grid, kBlock, 0, s>>>(io, phi, e0, ne, d->n_ev, nrhs, (const double2 *)c_dev, w, n);
+    };
+    // right-hand sides per thread: the smallest of 1, 4, 16 that holds them (16 a pass beyond)
+    auto pick = [&](auto zero, auto *io, const auto *phi) {
+      using C = decltype(zero);
+      using SE = std::remove_reference_t<decltype(*io)>;
+      if (nrhs == 1) go(correct_w_kernel<C, SE, 1>, io, phi, 1);
+      else if (nrhs <= 4) go(correct_w_kernel<C, SE, 4>, io, phi, 4);
+      else go(correct_w_kernel<C, SE, 16>, io, phi, 16);
+    };
+    if (spin_dt == OVL_F64) pick(0.0, (double2 *)inout, (const double2 *)d->phi_store);
+    else pick(0.0f, (float2 *)inout, (const float2 *)d->phi_store);
     HIP_TRY(hipGetLastError());
   }
   return OVL_OK;
