@@ -374,7 +374,9 @@ int ovl_overlap_solve_gmresr(const ovl_gauge *g, const ovl_poly *p, const ovl_de
  * (spb, order, remap, rb).  Order 1 = t-streaming tile order, 0 = memory order, with spb = 8
  * (eight threads per site: forward and backward hops on separate threads), 16 or 64 (four threads
  * per site) or 128 (two x-adjacent sites per lane).  Order 2 = LDS slab of whole x lines with
- * spb = 64, 128, 192 or 256 sites (single problems; spb a multiple of Lx dividing Lx Ly).
+ * spb = 64, 128, 192 or 256 sites (single problems; spb a multiple of Lx dividing Lx Ly).  Order 3 =
+ * plain steps in the t-marching form (tiles of whole x lines marched through t, up to 256 sites a
+ * tile; the final step as order 1), spb = 64, rb = 1.
  * Remap = XCD-contiguous workgroup ranges on or off.  rb = right-hand-side block: 1, 2 or 4
  * right-hand sides per thread reusing one read of the thread's two links (spb 16 or 64, orders
  * 0 and 1).  Each candidate runs 2 untimed and 10 timed steps that read the items' inputs and
@@ -396,9 +398,11 @@ int ovl_autotune_load(const char *cache_path);
 /* The configuration the library will use for a single problem: cfg_out = {sites per workgroup,
  * order, remap} (see ovl_autotune).  Defaults: 8 sites per workgroup below 4K
  * site-right-hand-sides, 16 below 64K, else 64 in tile order, with 128 (two sites per lane) for
- * FP32 links from 512K site-right-hand-sides; remap on; rb 1.  Two sites per lane need FP32
+ * FP32 links from 512K site-right-hand-sides; order 3 with 64 where a tile fits every lattice and a
+ * step's vectors and links exceed 256 MB; remap on; rb 1.  Two sites per lane need FP32
  * spinors, an even Lx and 16-byte aligned vectors (a call whose vectors are not aligned runs
- * with 64); a slab entry that does not fit the lattice falls back to the default. */
+ * with 64); a slab or t-marching entry that does not fit the lattice falls back to the
+ * default. */
 int ovl_launch_config(const ovl_gauge *g, int nrhs, int spin_dt, int cfg_out[3]);
 /* The configuration an evaluation of this problem set will use (the batched launch for several
  * items, the single-problem launch for one): cfg_out = {spb, order, remap, rb}, with the items'

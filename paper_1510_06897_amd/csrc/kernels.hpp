@@ -85,6 +85,9 @@ struct StepItem {
   // Right-hand-side groups of the workgroup order: right-hand-side blocks run fastest inside
   // groups of rgroup blocks, then the site blocks, then the groups (0: one group of all).
   int rgroup;
+  // Plan of the t-marching form (march.hpp; ct = 0: not planned): tile Lx x mty x mtz, t slices per
+  // workgroup, right-hand sides per group of its workgroup order, first workgroup.
+  int mty, mtz, ct, mgroup, mblk0;
 };
 
 // item-local workgroup lb -> (right-hand-side block rb, site block b) for nrb right-hand-side
@@ -125,6 +128,7 @@ struct StepArgs {
   int v_g5, src_g5, y_g5, mode, remap, n_items;
   int r12;                // TABLE: every item allows two-row link reads
   int total_blocks;       // workgroups of the launch
+  int march_blocks;       // workgroups of the t-marching form (0: not planned)
   const StepItem *table;  // TABLE: n_items items in device memory
   StepItem item;          // !TABLE: the one problem
 };

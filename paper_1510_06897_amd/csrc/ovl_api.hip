@@ -20,6 +20,7 @@
 
 #include "../../include/ovl.h"
 #include "kernels.hpp"
+#include "march.hpp"
 #include "stout.hpp"
 #include "solver.hpp"
 
@@ -252,13 +253,15 @@ void step_tile(const Geom &g, int spb, int site_bytes, int &ty, int &tz) {
 }
 
 // Launch configuration of the fused step kernel: sites per workgroup, workgroup order (memory
-// order, t-streaming tiles where a tile fits, or the LDS slab), the XCD-contiguous workgroup
-// remap and the right-hand-side block (right-hand sides per thread sharing one link read).
+// order, t-streaming tiles where a tile fits, the LDS slab, or plain steps in the t-marching form with
+// the final step in tiles), the XCD-contiguous workgroup remap and the right-hand-side block
+// (right-hand sides per thread sharing one link read).
 // Default rules unless ovl_autotune measured a better one for the same problem set: the
 // precision and the (extents, right-hand-side count) of every item of the launch, in order.
 struct LaunchCfg {
   int spb, tiles, remap, rb;
 };
+constexpr int kMarch = 3;  // LaunchCfg::tiles of the t-marching form (spb 64, rb 1)
 struct TuneKey {
   int prec;
   int r12;                                // two-row link reads (every item's field allows them)
@@ -273,6 +276,75 @@ std::map<TuneKey, LaunchCfg> g_tuned;
 LaunchCfg default_cfg(int64_t work, int prec = P_F64) {
   const int spb = (prec == P_F32 && work >= 512 * 1024) ? 128 : launch_spb(work);
   return LaunchCfg{spb, 1, 1, 1};
+}
+
+// Tile of the t-marching form for a lattice: whole x lines, ty x tz in (y, z) dividing the extents,
+// n = Lx ty tz sites in whole waves, at most kMarchThreads, and no more face sites than that; the
+// links' t slices must be whole 64-site blocks.  Among the tiles the one with the fewest face sites
+// per site wins.  Returns n (0: none fits).
+int march_tile(const Geom &g, int &ty, int &tz) {
+  ty = tz = 0;
+  if ((int64_t)g.L[0] * g.L[1] * g.L[2] % 64 || g.L[0] > kMarchThreads) return 0;
+  int64_t best = 0, bh = 0;
+  for (int a = 1; a <= g.L[1] && g.L[0] * a <= kMarchThreads; ++a)
+    for (int b = 1; b <= g.L[2] && g.L[0] * a * b <= kMarchThreads; ++b) {
+      const int64_t n = (int64_t)g.L[0] * a * b;
+      if (g.L[1] % a || g.L[2] % b || n % 64) continue;
+      const int64_t h = (a < g.L[1] ? 2 * g.L[0] * b : 0) + (b < g.L[2] ? 2 * g.L[0] * a : 0);
+      if (h > kMarchThreads || (best && h * best >= bh * n)) continue;
+      best = n;
+      bh = h;
+      ty = a;
+      tz = b;
+    }
+  return (int)best;
+}
+bool march_ok(const StepItem *items, int n) {
+  int ty, tz;
+  for (int i = 0; i < n; ++i)
+    if (!march_tile(items[i].g, ty, tz)) return false;
+  return true;
+}
+
+// t slices per workgroup of a launch of `slices` tile slices: the longest of 4, 8, 16, 32 that
+// leaves 2048 workgroups (a chunk re-reads the slices before and after it, so longer is less
+// traffic: 64 FP64 vectors of 16^3 x 32 2.91, 2.78, 2.73 ms at 8, 16, 32; but a launch of few
+// workgroups ends in a nearly empty round: 12 vectors 263, 273, 288 us at 4, 8, 16).
+int march_chunk(int64_t slices) {
+  int ct = 4;
+  while (ct < 32 && slices / (2 * ct) >= 2048) ct *= 2;
+  return ct;
+}
+int64_t march_slices(const StepItem &it) {
+  int ty, tz;
+  const int n = march_tile(it.g, ty, tz);
+  return n ? (int64_t)it.g.V / n * it.nrhs : 0;
+}
+
+// Where the t-marching form is the default: the step's three vectors and the links exceed the 256 MB
+// last-level cache, and most sites lie in tiles of kMarchThreads sites.  Measured, one fused step in
+// the default form / t-marching, us: 16^3 x 32 FP64 3 vectors (302 MB with the links) 79.8 / 79.7,
+// 4 110 / 91, 12 341 / 263; FP32 6 vectors (265 MB) 69.7 / 67.2, 8 105 / 96, 12 166 / 142; 16-bit
+// links 4 vectors (170 MB) 43.3 / 38.6, 2 (94 MB) 25.0 / 27.7, 12 169 / 124; 16^3 x 64 FP64 1 vector
+// (302 MB) 64.4 / 54.0.  Below the cache size the form has too few workgroups (8^3 x 16, 12 FP64
+// vectors: 18.8 / 29.0), and 192-site tiles leave a quarter of the threads idle (12^3 x 24, 24 FP32
+// vectors: 93 / 103).
+bool march_pays(int prec, const StepItem *items, int n) {
+  int64_t bytes = 0, sites = 0, full = 0;
+  for (int i = 0; i < n; ++i) {
+    const int64_t w = (int64_t)items[i].g.V * items[i].nrhs;
+    const int link = prec == P_F64 ? 16 : prec == P_F32 ? 8 : 4;
+    bytes += 3 * 12 * w * (prec == P_F64 ? 16 : 8) + (int64_t)36 * items[i].g.V * link;
+    sites += w;
+  }
+  if (bytes < (int64_t)256 << 20) return false;
+  for (int i = 0; i < n; ++i) {
+    int ty, tz;
+    const int t = march_tile(items[i].g, ty, tz);
+    if (!t) return false;
+    if (t == kMarchThreads) full += (int64_t)items[i].g.V * items[i].nrhs;
+  }
+  return 2 * full >= sites;
 }
 
 TuneKey tune_key(int prec, const StepItem *items, int n) {
@@ -290,7 +362,11 @@ LaunchCfg lookup_cfg(int prec, const StepItem *items, int n, int64_t work) {
   const TuneKey k = tune_key(prec, items, n);
   std::lock_guard<std::mutex> lk(g_tune_mu);
   auto it = g_tuned.find(k);
-  return it == g_tuned.end() ? default_cfg(work, prec) : it->second;
+  if (it != g_tuned.end()) {
+    if (it->second.tiles != kMarch || march_ok(items, n)) return it->second;
+    return default_cfg(work, prec);
+  }
+  return march_pays(prec, items, n) ? LaunchCfg{64, kMarch, 1, 1} : default_cfg(work, prec);
 }
 LaunchCfg lookup_cfg(const Geom &g, int prec, int nrhs, int64_t work, int r12) {
   StepItem it;
@@ -322,7 +398,7 @@ bool pairs_ok(Prec prec, const StepItem *items, int n) {
 // right-hand-side blocks exist for the one-site forms with four threads per site (16 and 64
 // sites per workgroup) in the memory and tile orders
 bool rb_ok(const LaunchCfg &c) {
-  return c.rb == 1 || ((c.rb == 2 || c.rb == 4) && (c.spb == 16 || c.spb == 64) && c.tiles != 2);
+  return c.rb == 1 || ((c.rb == 2 || c.rb == 4) && (c.spb == 16 || c.spb == 64) && c.tiles < 2);
 }
 LaunchCfg fit_cfg(LaunchCfg c, bool pairs) {
   if (c.spb == 128 && !pairs && c.tiles != 2) c.spb = 64;
@@ -354,8 +430,13 @@ int rhs_group_blocks(int nrhs, int rb) {
   return nrhs <= 16 ? 0 : std::max(1, kRhsGroup / rb);
 }
 
-// workgroup order and first workgroup of every item; returns the launch's workgroup count
-int plan_items(StepItem *items, int n, const LaunchCfg &cfg, int site_bytes) {
+int site_bytes_of(Prec prec);
+
+// workgroup order and first workgroup of every item, into the launch's arguments: the plan of the
+// step kernels and, with cfg.tiles == kMarch, that of the t-marching form of the plain steps
+template <bool TABLE>
+void plan_launch(StepArgs<TABLE> &p, StepItem *items, int n, const LaunchCfg &cfg, Prec prec) {
+  const int site_bytes = site_bytes_of(prec);
   int total = 0;
   for (int i = 0; i < n; ++i) {
     StepItem &it = items[i];
@@ -365,10 +446,31 @@ int plan_items(StepItem *items, int n, const LaunchCfg &cfg, int site_bytes) {
     // the slice budget covers every right-hand side of a group: they all pass through L2 between
     // a site and its t neighbour
     const int grhs = it.rgroup > 0 ? std::min(it.nrhs, it.rgroup * cfg.rb) : it.nrhs;
-    if (cfg.tiles == 1) step_tile(it.g, cfg.spb, site_bytes * grhs, it.ty, it.tz);
+    if (cfg.tiles == 1 || cfg.tiles == kMarch)
+      step_tile(it.g, cfg.spb, site_bytes * grhs, it.ty, it.tz);
+    it.ct = 0;
     total += item_blocks(it.g.V, cfg.spb) * ((it.nrhs + cfg.rb - 1) / cfg.rb);
   }
-  return total;
+  p.total_blocks = total;
+  p.remap = cfg.remap;
+  p.march_blocks = 0;
+  if (cfg.tiles != kMarch) return;
+  int64_t slices = 0;
+  for (int i = 0; i < n; ++i) slices += march_slices(items[i]);
+  const int ct = march_chunk(slices);
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    StepItem &it = items[i];
+    march_tile(it.g, it.mty, it.mtz);
+    const int tiles = it.g.L[1] / it.mty * (it.g.L[2] / it.mtz);
+    it.ct = std::min(ct, it.g.L[3]);
+    // the tiles of about 32 workgroups (an XCD's compute units) run side by side, so that faces are
+    // read from its L2
+    it.mgroup = std::max(1, 32 / tiles);
+    it.mblk0 = blocks;
+    blocks += it.nrhs * tiles * ((it.g.L[3] + it.ct - 1) / it.ct);
+  }
+  p.march_blocks = blocks;
 }
 
 int site_bytes_of(Prec prec) {
@@ -449,11 +551,30 @@ int launch_step_r(StepArgs<TABLE> &p, const LaunchCfg &cfg, hipStream_t s) {
   return OVL_OK;
 }
 
+// the t-marching form of a plain step
+template <class C, class SE, class LE, bool TABLE, bool R12>
+int launch_march(StepArgs<TABLE> &p, hipStream_t s) {
+  constexpr int bytes = march_lds_bytes<C>();
+  static std::once_flag once;
+  static hipError_t attr = hipSuccess;
+  std::call_once(once, [] {
+    attr = hipFuncSetAttribute((const void *)march_kernel<C, SE, LE, TABLE, R12>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  });
+  HIP_TRY(attr);
+  march_kernel<C, SE, LE, TABLE, R12><<<p.march_blocks, kMarchThreads, bytes, s>>>(p);
+  HIP_TRY(hipGetLastError());
+  return OVL_OK;
+}
+
 // two-row link reads where the problem's field allows them (single problem: its handle; a
 // table launch: every item's, recorded in p.r12 when the table was written)
 template <class C, class SE, class LE, bool TABLE>
 int launch_step(StepArgs<TABLE> &p, const LaunchCfg &cfg, hipStream_t s) {
   const bool r12 = TABLE ? p.r12 != 0 : p.item.r12 != 0;
+  if (p.march_blocks > 0 && p.mode == MODE_STEP)
+    return r12 ? launch_march<C, SE, LE, TABLE, true>(p, s)
+               : launch_march<C, SE, LE, TABLE, false>(p, s);
   return r12 ? launch_step_r<C, SE, LE, TABLE, true>(p, cfg, s)
              : launch_step_r<C, SE, LE, TABLE, false>(p, cfg, s);
 }
@@ -470,8 +591,7 @@ int dispatch_step(Prec prec, StepArgs<TABLE> &p, const LaunchCfg &cfg, hipStream
 
 // single problem: plan its item with the tuned (or default) configuration, then launch
 int dispatch_cfg(Prec prec, StepArgs<false> &p, const LaunchCfg &cfg, hipStream_t s) {
-  p.total_blocks = plan_items(&p.item, 1, cfg, site_bytes_of(prec));
-  p.remap = cfg.remap;
+  plan_launch(p, &p.item, 1, cfg, prec);
   return dispatch_step(prec, p, cfg, s);
 }
 int dispatch_single(Prec prec, StepArgs<false> &p, hipStream_t s) {
@@ -808,8 +928,7 @@ int run_sign_jobs(const SignJob *jobs, int nj, const ovl_poly *p, int mode, doub
   StepArgs<TABLE> args;
   clear_args(args);
   args.n_items = nj;
-  args.total_blocks = plan_items(items, nj, cfg, site_bytes_of(prec));
-  args.remap = cfg.remap;
+  plan_launch(args, items, nj, cfg, prec);
   args.r12 = 1;
   for (int j = 0; j < nj; ++j) args.r12 = args.r12 && items[j].r12;
   if (TABLE) {
@@ -960,7 +1079,7 @@ int check_batch(const ovl_batch_item *items, int n_items, int spin_dt, SignJob *
 bool cfg_valid(const LaunchCfg &c) {
   const bool ok_spb = c.tiles == 2 ? (c.spb == 64 || c.spb == 128 || c.spb == 192 || c.spb == 256)
                                    : (c.spb == 8 || c.spb == 16 || c.spb == 64 || c.spb == 128);
-  return ok_spb && c.tiles >= 0 && c.tiles <= 2 && rb_ok(c);
+  return ok_spb && c.tiles >= 0 && (c.tiles <= 2 || (c.tiles == kMarch && c.spb == 64)) && rb_ok(c);
 }
 int load_tune_cache(const char *path) {
   FILE *f = std::fopen(path, "r");
@@ -2818,6 +2937,7 @@ int ovl_autotune(const ovl_batch_item *items, int n_items, const ovl_poly *p, in
           }
           cands.push_back(c);
         }
+  if (march_ok(its, n_items)) cands.push_back(LaunchCfg{64, kMarch, 1, 1});
   if (!table)
     for (int spb : {64, 128, 192, 256})
       if (slab_ok(its[0].g, spb, prec))
@@ -2838,8 +2958,7 @@ int ovl_autotune(const ovl_batch_item *items, int n_items, const ovl_poly *p, in
   for (size_t ci = 0; ci < cands.size(); ++ci) {
     const LaunchCfg &cfg = cands[ci];
     if (table) {
-      at.total_blocks = plan_items(its, n_items, cfg, sb);
-      at.remap = cfg.remap;
+      plan_launch(at, its, n_items, cfg, prec);
       for (int i = 0; i < n_items && rc == OVL_OK; ++i) {
         write_item_kernel<<<1, 64, 0, s>>>(its[i], table_dev + i);
         if (hipGetLastError() != hipSuccess) rc = fail(OVL_EHIP, "item table write");
