@@ -52,6 +52,13 @@ __host__ __device__ __forceinline__ cx<T> cjmadd(cx<T> acc, cx<T> a, cx<T> b) {
   return acc;
 }
 
+// Orders the arithmetic that produces x before the loads that follow in the source: without it the
+// compiler moves arithmetic down to its use and keeps every operand of several hops in registers.
+template <class C>
+__device__ __forceinline__ void pin(cx<C> &x) {
+  asm volatile("" : "+v"(x.re), "+v"(x.im));
+}
+
 // Third row of an SU(3) matrix from the first two: unitarity and det = 1 give
 // row2 = conj(row0 x row1).  Links kept with two rows are read as six elements and completed
 // here (the stored third row is not read).

@@ -81,13 +81,6 @@ __device__ __forceinline__ void load_link_off(rsrc_t U, uint32_t ls, uint32_t vo
     for (int b = 0; b < 3; ++b) m[a][b] = bio<LE, C>::ld(U, voff, soff + (a * 3 + b) * ls);
 }
 
-// Orders the arithmetic that produces x before the loads that follow in the source: without it the
-// compiler moves arithmetic down to its use and keeps every operand of several hops in registers.
-template <class C>
-__device__ __forceinline__ void pin(cx<C> &x) {
-  asm volatile("" : "+v"(x.re), "+v"(x.im));
-}
-
 constexpr int kMarchThreads = 256;  // most sites of a tile, and most face sites
 // LDS bytes of a workgroup: 12 components of the tile and its faces
 template <class C>

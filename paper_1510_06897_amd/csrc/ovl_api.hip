@@ -3134,6 +3134,24 @@ int check_stout(const int32_t dims[4], double rho, double eps, int steps, Geom &
   return OVL_OK;
 }
 
+// t-streaming tile of the path kernels: the smallest whose slice is whole 256-site workgroups (none:
+// memory order)
+StoutOrder stout_order(const Geom &g) {
+  StoutOrder best{0, 0};
+  for (int ty = 2; ty <= 8; ty *= 2)
+    for (int tz = 2; tz <= 8; tz *= 2) {
+      if (g.L[1] % ty || g.L[2] % tz || (int64_t)g.L[0] * ty * tz % 256) continue;
+      if (!best.ty || ty * tz < best.ty * best.tz) best = StoutOrder{ty, tz};
+    }
+  return best;
+}
+int stout_staples(const double2 *U, double2 *C, double wp, double wr, const Geom &geo, hipStream_t s) {
+  stout_staple_kernel<<<4u * (unsigned)((geo.V + 255) / 256), 256, 0, s>>>(U, C, wp, wr, geo,
+                                                                           stout_order(geo));
+  HIP_TRY(hipGetLastError());
+  return OVL_OK;
+}
+
 void stout_weights(double rho, double eps, double &wp, double &wr) {
   wp = rho * (5.0 - 2.0 * eps) / 3.0;
   wr = -rho * (1.0 - eps) / 12.0;
@@ -3159,7 +3177,8 @@ int ovl_stout_smear(const int32_t dims[4], void *U_out, const void *U_in, double
   }
   double wp, wr;
   stout_weights(rho, eps, wp, wr);
-  // levels ping-pong through two work fields; the last step writes U_out
+  // levels ping-pong through two work fields, the last step writes U_out; a step's staple sums form in
+  // its output
   Scratch sc;
   const size_t fb = (bytes + 255) / 256 * 256;
   if (steps > 1 && (rc = scratch_alloc(sc, 2 * fb, s))) return rc;
@@ -3167,7 +3186,8 @@ int ovl_stout_smear(const int32_t dims[4], void *U_out, const void *U_in, double
   const double2 *cur = (const double2 *)U_in;
   for (int k = 0; k < steps; ++k) {
     double2 *dst = k == steps - 1 ? (double2 *)U_out : (double2 *)((char *)sc.p + (k % 2) * fb);
-    stout_step_kernel<<<grid, 256, 0, s>>>(cur, dst, nullptr, wp, wr, geo);
+    if ((rc = stout_staples(cur, dst, wp, wr, geo, s))) return rc;
+    stout_exp_kernel<<<grid, 256, 0, s>>>(cur, dst, dst, geo.V);
     HIP_TRY(hipGetLastError());
     cur = dst;
   }
@@ -3192,34 +3212,37 @@ int ovl_stout_backward(const int32_t dims[4], void *G_thin, const void *G_smeare
   }
   double wp, wr;
   stout_weights(rho, eps, wp, wr);
-  // work fields: levels 1 .. steps-1 of the forward smearing and the staple sums of levels
-  // 0 .. steps-2 (both from the regenerating forward pass), Gamma, the direct part and two
-  // derivative fields between the steps
+  // work fields: levels 1 .. steps-1 of the forward smearing and the staple sums of every level (both
+  // from the regenerating forward pass), Gamma, the direct part and two derivative fields between the
+  // steps; the last level's staple sums form in the field that later takes the first derivative
   const size_t fb = (bytes + 255) / 256 * 256;
   const int nlev = steps - 1;
-  const int nder = steps >= 3 ? 2 : (steps == 2 ? 1 : 0);
+  const int nder = steps >= 3 ? 2 : 1;
   Scratch sc;
   if ((rc = scratch_alloc(sc, (size_t)(2 * nlev + 2 + nder) * fb, s))) return rc;
   char *base = (char *)sc.p;
   auto field = [&](int i) { return (double2 *)(base + (size_t)i * fb); };
   double2 *gam = field(2 * nlev), *dir = field(2 * nlev + 1);
   const dim3 grid((unsigned)((geo.V + 255) / 256), 4);
-  std::vector<const double2 *> lev(steps), stap(steps, nullptr);
+  const StoutOrder order = stout_order(geo);
+  auto der = [&](int k) { return field(2 * nlev + 2 + (nder == 2 ? 1 - (k & 1) : 0)); };
+  std::vector<const double2 *> lev(steps), stap(steps);
   lev[0] = (const double2 *)U_thin;
-  for (int k = 1; k < steps; ++k) {
-    stout_step_kernel<<<grid, 256, 0, s>>>(lev[k - 1], field(k - 1), field(nlev + k - 1), wp, wr,
-                                           geo);
+  for (int k = 0; k < steps; ++k) {
+    double2 *c = k < nlev ? field(nlev + k) : der(k);
+    if ((rc = stout_staples(lev[k], c, wp, wr, geo, s))) return rc;
+    stap[k] = c;
+    if (k == nlev) break;
+    stout_exp_kernel<<<grid, 256, 0, s>>>(lev[k], c, field(k), geo.V);
     HIP_TRY(hipGetLastError());
-    lev[k] = field(k - 1);
-    stap[k - 1] = field(nlev + k - 1);
+    lev[k + 1] = field(k);
   }
   const double2 *gin = (const double2 *)G_smeared;
   for (int k = steps - 1; k >= 0; --k) {
-    double2 *gout =
-        k == 0 ? (double2 *)G_thin : field(2 * nlev + 2 + (nder == 2 ? 1 - (k & 1) : 0));
-    stout_back_local_kernel<<<grid, 256, 0, s>>>(lev[k], stap[k], gin, gam, dir, wp, wr, geo);
+    double2 *gout = k == 0 ? (double2 *)G_thin : der(k);
+    stout_back_local_kernel<<<grid, 256, 0, s>>>(lev[k], stap[k], gin, gam, dir, geo.V);
     HIP_TRY(hipGetLastError());
-    stout_back_gather_kernel<<<grid, 256, 0, s>>>(lev[k], gam, dir, gout, wp, wr, geo);
+    stout_back_gather_kernel<<<4u * grid.x, 256, 0, s>>>(lev[k], gam, dir, gout, wp, wr, geo, order);
     HIP_TRY(hipGetLastError());
     gin = gout;
   }

@@ -15,8 +15,8 @@
 // so a field must span less than 4 GiB.  A thread owns one link
 // (site, mu); the workgroup's 256 threads share mu, so the path loops below are uniform over a
 // wave.  exp(M) is a Taylor series after scaling M to norm <= 1/2, followed by squaring; the
-// derivative of exp comes from the same series for the Frechet derivative (the directional
-// derivative of every power, carried along the squarings).
+// derivative of exp comes from the same series for the Frechet derivative, carried along the
+// squarings.
 #pragma once
 
 #include "common.hpp"
@@ -143,12 +143,17 @@ __device__ __forceinline__ void store_m3(double2 *__restrict__ U, int dir, int s
 }
 
 // ---------------------------------------------------------------------------------------------
-// exp(A) and the Frechet derivative L(A, F) = d/dt exp(A + t F) at t = 0.
-//   Scale: X = A / 2^s with ||X||_F <= 1/2.  Series: T_0 = 1, T_{k+1} = X T_k / (k + 1) gives
-//   exp(X) = sum T_k; the derivative of X^k along F obeys D_{k+1} = F X^k + X D_k, so with
-//   S_k = D_k / k!:  S_1 = F, S_{k+1} = (F T_k + X S_k) / (k + 1) and L(X, F) = sum S_k.
+// exp(A) and the Frechet derivative L(A, F) = d/dt exp(A + t F) at t = 0 for traceless A.
+//   Scale: X = A / 2^s with ||X||_F <= 1/2.  Series: a traceless 3 x 3 matrix obeys (Cayley-Hamilton)
+//   X^3 = p X + q, p = tr(X^2) / 2, q = det X, so every term X^k / k! is a_k + b_k X + c_k X^2 with
+//   a' = c q / (k + 1), b' = (a + c p) / (k + 1), c' = b / (k + 1): the series runs on three complex
+//   numbers and exp(X) = f0 + f1 X + f2 X^2 takes one matrix product.  The derivative along a traceless
+//   G changes p by tr(X G) and q by tr(X^2 G):
+//     L(X, G) = f1 G + f2 (X G + G X) + df0 + df1 X + df2 X^2,  df = f_p tr(X G) + f_q tr(X^2 G),
+//   with the p and q derivatives of a, b, c carried along; a trace of F adds (tr F / 3) exp(X).
 //   Square: exp(2Y) = exp(Y)^2 and L(2Y, 2G) = L(Y, G) exp(Y) + exp(Y) L(Y, G).
-// 18 terms leave a remainder below 0.5^19 / 19! (1e-23) of the scaled series.
+// 18 terms leave a remainder below 0.5^19 / 19! (1e-23) of the scaled series.  (The same series as
+// matrix powers took 18 products for exp and 54 for the derivative.)
 constexpr int kExpTerms = 18;
 
 __device__ __forceinline__ int exp_scaling(const M3 &a) {
@@ -161,33 +166,108 @@ __device__ __forceinline__ int exp_scaling(const M3 &a) {
   return s;
 }
 
-__device__ inline M3 m3_exp(const M3 &a) {
-  const int s = exp_scaling(a);
-  const M3 x = m3_scale(a, ldexp(1.0, -s));
-  M3 e = m3_unit(), t = m3_unit();
-  for (int k = 1; k <= kExpTerms; ++k) {
-    t = m3_scale(m3_mul(x, t), 1.0 / k);
-    e = m3_axpy(e, 1.0, t);
+using cxd = cx<double>;
+__device__ __forceinline__ cxd cmul(cxd a, cxd b) { return cmadd(mk<double>(0.0, 0.0), a, b); }
+// tr(A B)
+__device__ __forceinline__ cxd m3_trmul(const M3 &a, const M3 &b) {
+  cxd t = mk<double>(0.0, 0.0);
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t = cmadd(t, a.e[i][k], b.e[k][i]);
+  return t;
+}
+__device__ __forceinline__ cxd m3_det(const M3 &a) {
+  cxd d = mk<double>(0.0, 0.0);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const int j = (i + 1) % 3, k = (i + 2) % 3;
+    const cxd m = cmadd(cmul(a.e[1][j], a.e[2][k]), -a.e[1][k], a.e[2][j]);
+    d = cmadd(d, a.e[0][i], m);
   }
+  return d;
+}
+// r += s A, s complex
+__device__ __forceinline__ void m3_cacc(M3 &r, cxd s, const M3 &a) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) r.e[i][j] = cmadd(r.e[i][j], s, a.e[i][j]);
+}
+__device__ __forceinline__ M3 m3_cdiag(cxd s) {
+  M3 r = m3_zero();
+#pragma unroll
+  for (int i = 0; i < 3; ++i) r.e[i][i] = s;
+  return r;
+}
+
+__device__ inline M3 m3_exp(const M3 &m) {
+  const int s = exp_scaling(m);
+  const M3 x = m3_scale(m, ldexp(1.0, -s));
+  const M3 x2 = m3_mul(x, x);
+  const cxd p = scale(x2.e[0][0] + x2.e[1][1] + x2.e[2][2], 0.5), q = m3_det(x);
+  cxd a = mk<double>(1.0, 0.0), b = mk<double>(0.0, 0.0), c = b;
+  cxd f0 = a, f1 = b, f2 = b;
+  for (int k = 1; k <= kExpTerms; ++k) {
+    const double r = 1.0 / k;
+    const cxd an = scale(cmul(c, q), r), bn = scale(cmadd(a, c, p), r), cn = scale(b, r);
+    a = an;
+    b = bn;
+    c = cn;
+    f0 = f0 + a;
+    f1 = f1 + b;
+    f2 = f2 + c;
+  }
+  M3 e = m3_cdiag(f0);
+  m3_cacc(e, f1, x);
+  m3_cacc(e, f2, x2);
   for (int i = 0; i < s; ++i) e = m3_mul(e, e);
   return e;
 }
 
 // exp(A) into *e and L(A, F) into *l
-__device__ inline void m3_exp_frechet(const M3 &a, const M3 &f, M3 *e_out, M3 *l_out) {
-  const int s = exp_scaling(a);
+__device__ inline void m3_exp_frechet(const M3 &m, const M3 &f, M3 *e_out, M3 *l_out) {
+  const int s = exp_scaling(m);
   const double sc = ldexp(1.0, -s);
-  const M3 x = m3_scale(a, sc), g = m3_scale(f, sc);
-  M3 e = m3_unit(), t = m3_unit();
-  M3 l = m3_zero(), d = m3_zero();
+  const M3 x = m3_scale(m, sc);
+  M3 g = m3_scale(f, sc);
+  const cxd tr = scale(g.e[0][0] + g.e[1][1] + g.e[2][2], 1.0 / 3.0);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) g.e[i][i] = g.e[i][i] - tr;
+  const M3 x2 = m3_mul(x, x);
+  const cxd p = scale(x2.e[0][0] + x2.e[1][1] + x2.e[2][2], 0.5), q = m3_det(x);
+  const cxd dp = m3_trmul(x, g), dq = m3_trmul(x2, g);
+  const cxd zero = mk<double>(0.0, 0.0);
+  cxd a = mk<double>(1.0, 0.0), b = zero, c = zero;
+  cxd ad = zero, bd = zero, cd = zero;  // derivatives of a, b, c along (dp, dq)
+  cxd f0 = a, f1 = zero, f2 = zero, g0 = zero, g1 = zero, g2 = zero;
   for (int k = 1; k <= kExpTerms; ++k) {
-    // S_k = (F T_{k-1} + X S_{k-1}) / k, T_k = X T_{k-1} / k  (S_0 = 0, T_0 = 1)
-    const M3 dn = m3_scale(m3_axpy(m3_mul(g, t), 1.0, m3_mul(x, d)), 1.0 / k);
-    t = m3_scale(m3_mul(x, t), 1.0 / k);
-    d = dn;
-    e = m3_axpy(e, 1.0, t);
-    l = m3_axpy(l, 1.0, d);
+    const double r = 1.0 / k;
+    const cxd an = scale(cmul(c, q), r), bn = scale(cmadd(a, c, p), r), cn = scale(b, r);
+    const cxd adn = scale(cmadd(cmul(cd, q), c, dq), r);
+    const cxd bdn = scale(cmadd(cmadd(ad, cd, p), c, dp), r), cdn = scale(bd, r);
+    a = an;
+    b = bn;
+    c = cn;
+    ad = adn;
+    bd = bdn;
+    cd = cdn;
+    f0 = f0 + a;
+    f1 = f1 + b;
+    f2 = f2 + c;
+    g0 = g0 + ad;
+    g1 = g1 + bd;
+    g2 = g2 + cd;
   }
+  M3 e = m3_cdiag(f0);
+  m3_cacc(e, f1, x);
+  m3_cacc(e, f2, x2);
+  M3 l = m3_cdiag(g0);
+  m3_cacc(l, f1, g);
+  m3_cacc(l, g1, x);
+  m3_cacc(l, g2, x2);
+  m3_cacc(l, f2, m3_axpy(m3_mul(x, g), 1.0, m3_mul(g, x)));
+  m3_cacc(l, tr, e);
   for (int i = 0; i < s; ++i) {
     l = m3_axpy(m3_mul(l, e), 1.0, m3_mul(e, l));
     e = m3_mul(e, e);
@@ -357,20 +437,50 @@ __device__ inline M3 staple_sum(rsrc_t U, const SiteCoord &x, int site, int mu, 
   return c;
 }
 
-// One smearing step: out_mu(x) = exp(TA(C_mu(x) U_mu(x)^+)) U_mu(x).  Grid (ceil(V / 256), 4).
-// C_out (nullable) receives the staple sums for the chain rule.
+// Workgroup order of the path kernels: a launch of 4 ceil(V / 256) workgroups, XCD-contiguous ranges,
+// the four directions of 256 sites side by side; the sites in memory order, or (ty > 0) in t-streaming
+// tiles -- whole x lines, ty x tz in (y, z), consecutive workgroups walking t.  The paths of the four
+// directions run over the same links, so what one workgroup reads its neighbours on the XCD find in
+// L2.  (With the directions one after the other over the whole lattice and workgroups dealt round
+// robin to the XCDs the kernels waited for L2 misses: three steps of 24^3 x 48 take 6.1 ms forward and
+// 20.3 ms backward instead of 13.2 and 41.2, of 16^3 x 32 1.39 and 4.20 instead of 2.1 and 7.8.)
+struct StoutOrder {
+  int ty, tz;
+};
+__device__ __forceinline__ int stout_site(const Geom &g, StoutOrder o, int &mu) {
+  const int gb = xcd_block(blockIdx.x, gridDim.x, 1);
+  mu = gb & 3;
+  if (o.ty <= 0) return (gb >> 2) * 256 + threadIdx.x;
+  const int slice = g.L[0] * o.ty * o.tz, nsub = slice / 256;
+  const int tb = (gb >> 2) / nsub;
+  const int local = ((gb >> 2) - tb * nsub) * 256 + threadIdx.x;
+  const int t = tb % g.L[3], tile = tb / g.L[3], nty = g.L[1] / o.ty;
+  const int x = local % g.L[0], row = local / g.L[0];
+  const int y = (tile % nty) * o.ty + row % o.ty, z = (tile / nty) * o.tz + row / o.ty;
+  return x + g.stride[1] * y + g.stride[2] * z + g.stride[3] * t;
+}
+
+// C_mu(x) of every link.  146 registers, three waves per SIMD (bounded to 128 for four: 373 -> 415 us
+// at 16^3 x 32).
 __global__ void __launch_bounds__(256)
-    stout_step_kernel(const double2 *__restrict__ U, double2 *__restrict__ out,
-                      double2 *__restrict__ C_out, double wp, double wr, Geom g) {
+    stout_staple_kernel(const double2 *__restrict__ U, double2 *__restrict__ C, double wp, double wr,
+                        Geom g, StoutOrder order) {
+  int mu;
+  const int site = stout_site(g, order, mu);
+  if (site >= g.V) return;
+  store_m3(C, mu, site, g.V,
+           staple_sum(make_rsrc(U, 576u * (uint32_t)g.V), site_coord(site, g), site, mu, wp, wr, g));
+}
+
+// One smearing step from the staple sums: out_mu(x) = exp(TA(C_mu(x) U_mu(x)^+)) U_mu(x).  out may be C.
+// Grid (ceil(V / 256), 4).  Apart from the staple kernel, which then needs fewer registers.
+__global__ void __launch_bounds__(256)
+    stout_exp_kernel(const double2 *U, const double2 *C, double2 *out, int V) {
   const int site = blockIdx.x * 256 + threadIdx.x;
   const int mu = blockIdx.y;
-  if (site >= g.V) return;
-  const SiteCoord x = site_coord(site, g);
-  const M3 c = staple_sum(make_rsrc(U, 576u * (uint32_t)g.V), x, site, mu, wp, wr, g);
-  if (C_out) store_m3(C_out, mu, site, g.V, c);
-  const M3 u = load_m3(U, mu, site, g.V);
-  const M3 e = m3_exp(m3_ta(m3_muld(c, u)));
-  store_m3(out, mu, site, g.V, m3_mul(e, u));
+  if (site >= V) return;
+  const M3 c = load_m3(C, mu, site, V), u = load_m3(U, mu, site, V);
+  store_m3(out, mu, site, V, m3_mul(m3_exp(m3_ta(m3_muld(c, u))), u));
 }
 
 // Backward of one step, the part local to each link.  With G' = dL/dRe U' + i dL/dIm U' of the
@@ -378,27 +488,24 @@ __global__ void __launch_bounds__(256)
 //   dL/dE = G' U^+,  dL/dM = L(M^+, dL/dE)  (the adjoint of the Frechet derivative of exp at M),
 //   dL/dOmega = (g - g^+)/2 - (i/3) Im tr(g) for g = dL/dM  (M = TA(Omega)),
 //   Gamma = dL/dC = dL/dOmega U,   direct = E^+ G' + (dL/dOmega)^+ C.
-// Writes Gamma and the direct part of dL/dU.  C_in (nullable): the level's staple sums.
+// Writes Gamma and the direct part of dL/dU; C: the level's staple sums.  Grid (ceil(V / 256), 4).
 __global__ void __launch_bounds__(256)
-    stout_back_local_kernel(const double2 *__restrict__ U, const double2 *__restrict__ C_in,
+    stout_back_local_kernel(const double2 *__restrict__ U, const double2 *__restrict__ C,
                             const double2 *__restrict__ gout, double2 *__restrict__ gamma,
-                            double2 *__restrict__ direct, double wp, double wr, Geom g) {
+                            double2 *__restrict__ direct, int V) {
   const int site = blockIdx.x * 256 + threadIdx.x;
   const int mu = blockIdx.y;
-  if (site >= g.V) return;
-  // the staple sums of this level from the forward pass when available
-  const M3 c = C_in ? load_m3(C_in, mu, site, g.V)
-                    : staple_sum(make_rsrc(U, 576u * (uint32_t)g.V), site_coord(site, g), site, mu,
-                                 wp, wr, g);
-  const M3 u = load_m3(U, mu, site, g.V);
+  if (site >= V) return;
+  const M3 c = load_m3(C, mu, site, V);
+  const M3 u = load_m3(U, mu, site, V);
   const M3 m = m3_ta(m3_muld(c, u));
-  const M3 gp = load_m3(gout, mu, site, g.V);
+  const M3 gp = load_m3(gout, mu, site, V);
   // exp(M^+) = exp(-M) = E^+ (M is anti-Hermitian), and dL/dM = L(M^+, G' U^+)
   M3 ed, gm;
   m3_exp_frechet(m3_scale(m, -1.0), m3_muld(gp, u), &ed, &gm);
   const M3 go = m3_ta(gm);
-  store_m3(gamma, mu, site, g.V, m3_mul(go, u));
-  store_m3(direct, mu, site, g.V, m3_axpy(m3_mul(ed, gp), 1.0, m3_dmul(go, c)));
+  store_m3(gamma, mu, site, V, m3_mul(go, u));
+  store_m3(direct, mu, site, V, m3_axpy(m3_mul(ed, gp), 1.0, m3_dmul(go, c)));
 }
 
 // Backward of one step, the staple part.  Link (y, d) receives w A^+ Gamma_nu(x) B^+ (its adjoint
@@ -409,7 +516,7 @@ __global__ void __launch_bounds__(256)
 // (the staple sum is the gradient of the gauge action, whose second derivative is symmetric).  So
 // each link walks its own 24 paths once, carrying the product X and its derivative T:
 //   X <- X F,  T <- T F + X Gamma(F).
-// out = direct + sum_paths w T: dL/dU of the step's input.  Grid (ceil(V / 256), 4).
+// out = direct + sum_paths w T: dL/dU of the step's input.
 // factor of path step (dir, sgn) at `pos` of U and the same link of Gamma (both daggered for a
 // backward step); pos is advanced
 __device__ __forceinline__ void path_factor2(rsrc_t U, rsrc_t Gm, const PlaneAddr &pa, int &a,
@@ -433,9 +540,9 @@ __device__ __forceinline__ void path_factor2(rsrc_t U, rsrc_t Gm, const PlaneAdd
 __global__ void __launch_bounds__(256)
     stout_back_gather_kernel(const double2 *__restrict__ U, const double2 *__restrict__ gamma,
                              const double2 *__restrict__ direct, double2 *__restrict__ out,
-                             double wp, double wr, Geom g) {
-  const int site = blockIdx.x * 256 + threadIdx.x;
-  const int d = blockIdx.y;
+                             double wp, double wr, Geom g, StoutOrder order) {
+  int d;
+  const int site = stout_site(g, order, d);
   if (site >= g.V) return;
   const SiteCoord y = site_coord(site, g);
   const rsrc_t ru = make_rsrc(U, 576u * (uint32_t)g.V);
