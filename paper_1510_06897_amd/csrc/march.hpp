@@ -210,12 +210,11 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
   const bool has_src = pa != 0.0, has_w = p.w_role != ROLE_NONE;
   const rsrc_t sr = make_rsrc(role_vec<SE>(I, has_src ? ROLE_PSI : p.v_role, r, ex.V), has_src ? vb : 0u);
   const rsrc_t w = make_rsrc(role_vec<SE>(I, has_w ? p.w_role : p.v_role, r, ex.V), has_w ? vb : 0u);
-  // coefficients of the upper and the lower spin pair: gamma5 on the input, the output (y_g5) and psi
-  // (src_g5) are signs of the lower ones
+  // gamma5 on the input, the output (y_g5) and psi (src_g5): signs of the lower spin pair
   const C s5 = p.v_g5 ? C(-1) : C(1);
   const C sy = p.y_g5 ? C(-1) : C(1);
   const C al = C(pa), ah = p.src_g5 ? C(-pa) : C(pa), tw = C(p.t);
-  const C kd = C(p.kd), kdl = sy * s5 * kd, kh = C(p.kh), khl = sy * kh;
+  const C kd = C(p.kd), kh = C(p.kh);
 
   cx<C> pu[2][3], pd[2][3], hu[2][3], hd[2][3];  // t + 1 slice: own and face site
   cx<C> bt[2][3];                                // U_t^+(t - 1) h(t - 1)
@@ -277,73 +276,86 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
   using I2 = std::integral_constant<int, 2>;
   using M1 = std::integral_constant<int, -1>;
   // Loads complete in issue order, so each group is issued after everything that is waited for
-  // before it: x and y links (issued before the barrier), psi and the z links, the t + 1 slice,
-  // w and the t link.
+  // before it: x and y links (issued before the barrier), the z links, the t + 1 slice, the t link,
+  // psi and w.
   for (int t = t0; t < t1; ++t) {
     if (active) {
       const uint32_t so = (uint32_t)t * ts;
-      cx<C> acc[12], base[12], sv[12];  // hopping sum, a psi + t w, operand in flight
+      cx<C> acc[12], dir[12], wv[12], sv[12];  // hopping sum, one direction's part, w and psi
+      auto settle = [&](cx<C> *q) {
 #pragma unroll
-      for (int i = 0; i < 12; ++i) acc[i] = mk<C>(0, 0);
-      half_add<3, -1>(acc, bt);
-      auto settle = [&]() {
-#pragma unroll
-        for (int i = 0; i < 12; ++i) pin(acc[i]);
+        for (int i = 0; i < 12; ++i) pin(q[i]);
         __builtin_amdgcn_sched_barrier(0);
       };
       auto hop = [&](auto mu_, auto sg_, int j, cx<C> m[3][3]) {
         constexpr int MU = decltype(mu_)::value, SG = decltype(sg_)::value;
         cx<C> u[2][3], d[2][3], h[2][3], rr[2][3];
+        if (SG > 0) {
+#pragma unroll
+          for (int i = 0; i < 12; ++i) dir[i] = mk<C>(0, 0);
+        }
         get12(j, u, d);
         half_project<MU, SG>(u, d, s5, h);
         if (R12) su3_row2(m);
         half_mul<(SG < 0)>(m, h, rr);
-        half_add<MU, SG>(acc, rr);
-        settle();
+        half_add<MU, SG>(dir, rr);
+        settle(dir);
       };
-      auto own = [&](rsrc_t q) {
+      // the directions' parts are added in the order of the direction-split kernels, ((x + y) + z) + t
+      // with forward before backward, so that every launch form gives the same bits
+      auto add_dir = [&]() {
 #pragma unroll
-        for (int i = 0; i < 12; ++i) sv[i] = bio<SE, C>::ld(q, vo, so + i * cs);
+        for (int i = 0; i < 12; ++i) acc[i] = acc[i] + dir[i];
       };
       hop(I0{}, I1{}, jxp, k0);
       hop(I0{}, M1{}, jxm, k1);
-      own(sr);
+#pragma unroll
+      for (int i = 0; i < 12; ++i) acc[i] = dir[i];
+      settle(acc);
       link(lo, 2, t, k0);
       link(lz, 2, t, k1);
       __builtin_amdgcn_sched_barrier(0);
       hop(I1{}, I1{}, jyp, k2);
       hop(I1{}, M1{}, jym, k3);
-#pragma unroll
-      for (int i = 0; i < 12; ++i) {
-        base[i] = scale(sv[i], i < 6 ? al : ah);
-        pin(base[i]);
-      }
+      add_dir();
+      settle(acc);
       const int tn = t + 1 == ex.lt ? 0 : t + 1;
       load12(vo, tn, pu, pd);
       if (hactive && t + 1 < t1) load12(vh, tn, hu, hd);
       __builtin_amdgcn_sched_barrier(0);
       hop(I2{}, I1{}, jzp, k0);
       hop(I2{}, M1{}, jzm, k1);
-      own(w);
+      add_dir();
+      settle(acc);
       link(lo, 3, t, k2);
+#pragma unroll
+      for (int i = 0; i < 12; ++i) sv[i] = bio<SE, C>::ld(sr, vo, so + i * cs);
+#pragma unroll
+      for (int i = 0; i < 12; ++i) wv[i] = bio<SE, C>::ld(w, vo, so + i * cs);
       __builtin_amdgcn_sched_barrier(0);
-      // own site: the half-spinor carried to t + 1 and the diagonal term; t forward
+      // t forward with the t + 1 slice, t backward with the carried half-spinor, and the one carried on
       cx<C> u[2][3], d[2][3], h[2][3], rr[2][3];
+#pragma unroll
+      for (int i = 0; i < 12; ++i) dir[i] = mk<C>(0, 0);
+      half_project<3, 1>(pu, pd, s5, h);
+      if (R12) su3_row2(k2);
+      half_mul<false>(k2, h, rr);
+      half_add<3, 1>(dir, rr);
+      half_add<3, -1>(dir, bt);
+      add_dir();
+      settle(acc);
       get12(sj, u, d);
       half_project<3, -1>(u, d, s5, h);
+      half_mul<true>(k2, h, bt);
 #pragma unroll
       for (int i = 0; i < 12; ++i) {
-        const cx<C> x = i < 6 ? u[i / 3][i % 3] : d[i / 3 - 2][i % 3];
-        base[i] = base[i] + scale(x, i < 6 ? kd : kdl) + scale(sv[i], tw);
-        pin(base[i]);
+        const cx<C> v0 = i < 6 ? u[i / 3][i % 3] : d[i / 3 - 2][i % 3];
+        const cx<C> xv = i < 6 ? v0 : mk<C>(s5 * v0.re, s5 * v0.im);
+        cx<C> yv = mk<C>(kd * xv.re + kh * acc[i].re, kd * xv.im + kh * acc[i].im);
+        if (i >= 6) yv = mk<C>(sy * yv.re, sy * yv.im);
+        yv = yv + scale(sv[i], i < 6 ? al : ah);
+        acc[i] = yv + scale(wv[i], tw);
       }
-      if (R12) su3_row2(k2);
-      half_mul<true>(k2, h, bt);
-      half_project<3, 1>(pu, pd, s5, h);
-      half_mul<false>(k2, h, rr);
-      half_add<3, 1>(acc, rr);
-#pragma unroll
-      for (int i = 0; i < 12; ++i) acc[i] = base[i] + scale(acc[i], i < 6 ? kh : khl);
 #pragma unroll
       for (int i = 0; i < 12; ++i) bio<SE, C>::st(o, vo, so + i * cs, acc[i]);
     }
