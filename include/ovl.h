@@ -212,7 +212,10 @@ int ovl_wilson_link_vjp(const ovl_gauge *g, void *G_dev, const void *chi, const 
 
 /* G_dev = d Re <chi, p(X) psi> / dU with p the polynomial of the handle (no deflation term,
  * lmax held fixed): reverse Clenshaw sweep on chi with the forward Chebyshev vectors of psi
- * recomputed from checkpoints every ckpt_stride steps (0 = ceil(sqrt(N))).  The recomputation
+ * recomputed from checkpoints every ckpt_stride steps.  0: all N forward vectors are kept (N + 66
+ * vectors of work space, from the device's memory pool, which retains it for later calls) where that is
+ * at most a tenth of the device's memory and can be allocated, else checkpoints every ceil(sqrt(N))
+ * steps; under stream capture always checkpoints.  The recomputation
  * and the reverse sweep of a segment are independent, so their steps run two at a time in one
  * launch that reads the links once (the launch configuration of a two-right-hand-side problem on
  * this lattice, see ovl_autotune).  Layout of G_dev as in ovl_wilson_link_vjp; single right-hand

@@ -1313,7 +1313,8 @@ __global__ void __launch_bounds__(256) su3_row2_dev_kernel(const LE *U, int V, d
 // (ty > 0) the t-streaming tile order of the step kernels -- whole x lines, ty x tz in (y, z),
 // consecutive workgroups walking t -- so the t neighbours a workgroup reads were loaded shortly
 // before by the workgroup of the previous slice, and most y and z neighbours lie in its own
-// tile (measured: 3% faster than memory order at 24^3 x 48).
+// tile (measured: 3% faster than memory order at 24^3 x 48).  The workgroup ranges are XCD-contiguous
+// (FP64, 16^3 x 32, 8 pairs: 197 -> 174 us a launch; FP32, 24^3 x 48, 18 pairs: no difference).
 __device__ __forceinline__ int vjp_site(int gb, int sl, const Ext4 &ex, int ty, int tz) {
   if (ty <= 0) return gb * 64 + sl;
   const int slice = ex.lx * ty * tz;
@@ -1359,7 +1360,7 @@ __global__ void __launch_bounds__(256)
                     int out_mode, int ty, int tz) {
   const int mu = threadIdx.x >> 6, sl = threadIdx.x & 63;
   const Ext4 ex = ext_of(geo);
-  const int site = vjp_site(blockIdx.x, sl, ex, ty, tz);
+  const int site = vjp_site(xcd_block(blockIdx.x, gridDim.x, 1), sl, ex, ty, tz);
   // no early return: every thread reaches the barriers; inactive lanes load and store nothing
   const bool active = site < ex.V;
   const int s_site = active ? site : 0;

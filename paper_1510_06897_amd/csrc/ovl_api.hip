@@ -23,6 +23,7 @@
 #include "march.hpp"
 #include "stout.hpp"
 #include "solver.hpp"
+#include "workspace.hpp"
 
 namespace ovl {
 bool cheb_sign_coeffs(int degree, double eps, std::vector<double> &alpha);
@@ -61,7 +62,8 @@ int elem_bytes(int dt) { return dt == OVL_F64 ? 16 : dt == OVL_F32 ? 8 : dt == O
 
 std::atomic<uint64_t> g_poly_serial{1};
 
-// stream-ordered temporaries from the device's default pool, kept cached between calls
+// stream-ordered temporaries: blocks kept between calls, or (small, and while the stream is captured)
+// from the device's default pool
 std::once_flag g_pool_once[64];
 int setup_pool(int dev) {
   hipMemPool_t pool;
@@ -74,8 +76,10 @@ int setup_pool(int dev) {
 struct Scratch {
   void *p = nullptr;
   hipStream_t s = nullptr;
+  Block block;  // p's block, unless p is the pool's
   ~Scratch() {
-    if (p) (void)hipFreeAsync(p, s);
+    if (block.p) block_cache().give(block, s);
+    else if (p) (void)hipFreeAsync(p, s);
   }
 };
 
@@ -88,6 +92,15 @@ int scratch_alloc(Scratch &sc, size_t bytes, hipStream_t s) {
     if (rc != OVL_OK) return rc;
   }
   sc.s = s;
+  if (bytes >= kKeepBlock) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &cap));
+    if (cap == hipStreamCaptureStatusNone) {
+      HIP_TRY(block_cache().take(bytes, s, sc.block));
+      sc.p = sc.block.p;
+      return OVL_OK;
+    }
+  }
   HIP_TRY(hipMallocAsync(&sc.p, std::max<size_t>(bytes, 256), s));
   return OVL_OK;
 }
@@ -127,6 +140,7 @@ struct ovl_gauge {
   int device;
   uint64_t serial;    // unique per handle (keys the step-graph cache)
   int lstride;        // elements between link components inside a block (kLinkBlock)
+  Block mem;          // links and flags
   void *links;        // [ceil(V / 64)][4 * 3 * 3][64] complex in store_dt
   uint32_t *flags;    // sticky device flags
   int r12 = 0;        // kernels read two rows per link and complete the third (SU(3) fields)
@@ -1214,9 +1228,13 @@ int ovl_gauge_create(ovl_gauge **out, const int32_t dims[4], const void *U_dev, 
   g->serial = g_poly_serial.fetch_add(1);
   hipError_t e = hipGetDevice(&g->device);
   const int64_t n = (int64_t)36 * geo.V;
-  if (e == hipSuccess) e = hipMalloc(&g->links, nlink * elem_bytes(store_dt));
-  if (e == hipSuccess) e = hipMalloc((void **)&g->flags, 256);
-  if (e == hipSuccess) e = hipMemsetAsync(g->flags, 0, 256, s);
+  const size_t lbytes = ((size_t)nlink * elem_bytes(store_dt) + 255) / 256 * 256;
+  if (e == hipSuccess) e = block_cache().take(lbytes + 256, s, g->mem);
+  if (e == hipSuccess) {
+    g->links = g->mem.p;
+    g->flags = (uint32_t *)((char *)g->mem.p + lbytes);
+    e = hipMemsetAsync(g->flags, 0, 256, s);
+  }
   if (e == hipSuccess) {
     const int threads = 256;
     const unsigned blocks = (unsigned)((n + threads - 1) / threads);
@@ -1235,8 +1253,8 @@ int ovl_gauge_create(ovl_gauge **out, const int32_t dims[4], const void *U_dev, 
     e = hipGetLastError();
   }
   if (e != hipSuccess) {
-    if (g->links) (void)hipFree(g->links);
-    if (g->flags) (void)hipFree(g->flags);
+    (void)hipGetLastError();
+    block_cache().give(g->mem, s);
     delete g;
     return fail(e == hipErrorOutOfMemory ? OVL_ENOMEM : OVL_EHIP, "gauge create: %s",
                 hipGetErrorString(e));
@@ -1249,8 +1267,7 @@ int ovl_gauge_destroy(ovl_gauge *g) {
   g_err[0] = 0;
   if (!g) return OVL_OK;
   (void)hipDeviceSynchronize();
-  (void)hipFree(g->links);
-  (void)hipFree(g->flags);
+  block_cache().give(g->mem, nullptr);
   delete g;
   return OVL_OK;
 }
@@ -2200,6 +2217,32 @@ int launch_vjp(Prec prec, const ovl_gauge *g, void *G, double2 *G64, const void 
   return OVL_OK;
 }
 
+// Pairs per link-VJP launch of a force that keeps every t_m: fewer launches read and write the running
+// sum of G (FP64, 1152 bytes a site) less often; beyond 64 it is below 2% of a launch's bytes.
+constexpr int kForcePairs = 64;
+
+// Whether a force may take `bytes` of work space to keep every t_m: a tenth of the device's memory (read
+// once per device: hipMemGetInfo has stalled the host for 10 ms and more here); the allocation itself
+// tells whether they are free.  Not while the stream is captured: the graph would hold them.
+bool force_may_keep(size_t bytes, hipStream_t s) {
+  static std::once_flag once[64];
+  static size_t total[64];
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  int dev = -1;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+      hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+    (void)hipGetLastError();
+    return false;
+  }
+  std::call_once(once[dev], [dev] {
+    if (hipDeviceTotalMem(&total[dev], dev) != hipSuccess) {
+      (void)hipGetLastError();
+      total[dev] = 0;
+    }
+  });
+  return bytes <= total[dev] / 10;
+}
+
 }  // namespace
 
 extern "C" {
@@ -2235,33 +2278,53 @@ int ovl_sign_force(const ovl_gauge *g, const ovl_poly *p, void *G, const void *c
     return fail(OVL_EDIMS, "the FP64 sum of G over %d sites exceeds 4 GiB", g->g.V);
   if (ckpt_stride < 0) return fail(OVL_EINVAL, "ckpt_stride must be >= 0");
   const int N = (int)p->alpha.size() - 1;
-  int S = ckpt_stride > 0 ? ckpt_stride : (int)std::ceil(std::sqrt((double)N));
-  S = std::max(1, std::min(S, N));
-  const int nseg = (N + S - 1) / S;  // segments cover m = 0 .. N-1
-  // checkpoint slots: t_{jS} and t_{jS+1} of every segment j (distinct m only, m <= N-1)
-  std::vector<int> slot_of(N + 1, -1);
-  int nslot = 0;
-  for (int j = 0; j < nseg; ++j)
-    for (int m = j * S; m <= j * S + 1 && m <= N - 1; ++m)
-      if (slot_of[m] < 0) slot_of[m] = nslot++;
   hipStream_t s = as_stream(stream);
   const size_t vec = (size_t)12 * g->g.V * elem_bytes(spin_dt);
   const size_t vecp = (vec + 255) / 256 * 256;
-  // checkpoints, segment buffer of S vectors (+1 spare), ring of S + 2 Clenshaw vectors, and for
-  // FP32 spinors the FP64 running sum of G across the segments
-  const int R = S + 2;
-  const size_t nvec = (size_t)nslot + (S + 1) + R;
   const bool f64 = prec == P_F64;
-  const size_t g64_bytes = (!f64 && nseg > 1) ? (size_t)36 * g->g.V * sizeof(double2) : 0;
+  // Work space of a segment length: checkpoints, the segment buffer of S vectors (+1 spare), a ring of
+  // S + 2 Clenshaw vectors and, for FP32 spinors, the FP64 running sum of G across the segments.
+  // `keep`: every t_m has a slot of its own (nothing is regenerated, no segment buffer).
+  int S = 0, R = 0, nseg = 0, nslot = 0;
+  std::vector<int> slot_of;
+  size_t nvec = 0, g64_bytes = 0;
+  auto plan = [&](int stride, bool keep) {
+    S = std::max(1, std::min(stride, N));
+    R = S + 2;
+    nseg = (N + S - 1) / S;  // segments cover m = 0 .. N-1
+    // checkpoint slots: t_{jS} and t_{jS+1} of every segment j (distinct m only, m <= N-1)
+    slot_of.assign(N + 1, -1);
+    nslot = 0;
+    for (int j = 0; j < nseg; ++j)
+      for (int m = j * S; m <= (keep ? j * S + S - 1 : j * S + 1) && m <= N - 1; ++m)
+        if (slot_of[m] < 0) slot_of[m] = nslot++;
+    nvec = (size_t)nslot + (keep ? 0 : S + 1) + R;
+    g64_bytes = (!f64 && nseg > 1) ? (size_t)36 * g->g.V * sizeof(double2) : 0;
+  };
+  // Without a stride from the caller all t_m are kept where they take at most a tenth of the device's
+  // memory: the backward sweep then regenerates nothing (24^3 x 48 FP32, degree 299: 23 GB, 94.9 -> 77.5
+  // ms).  Otherwise, or where the allocation fails, checkpoints every ceil(sqrt N).
   Scratch sc;
-  rc = scratch_alloc(sc, nvec * vecp + g64_bytes, s);
-  if (rc) return rc;
+  bool keep = false;
+  if (ckpt_stride == 0) {
+    plan(kForcePairs, true);
+    const size_t bytes = nvec * vecp + g64_bytes;
+    if (force_may_keep(bytes, s)) {
+      rc = scratch_alloc(sc, bytes, s);
+      keep = rc == OVL_OK;
+      if (rc != OVL_OK && rc != OVL_ENOMEM) return rc;
+    }
+  }
+  if (!keep) {
+    plan(ckpt_stride > 0 ? ckpt_stride : (int)std::ceil(std::sqrt((double)N)), false);
+    if ((rc = scratch_alloc(sc, nvec * vecp + g64_bytes, s))) return rc;
+  }
   char *base = (char *)sc.p;
   double2 *G64 = f64 ? (double2 *)G : (g64_bytes ? (double2 *)(base + nvec * vecp) : nullptr);
   auto ck = [&](int m) -> void * { return base + (size_t)slot_of[m] * vecp; };
   auto seg = [&](int i) -> void * { return base + ((size_t)nslot + i) * vecp; };
   // b_k lives in ring slot k mod R: a segment touches b_{m0} .. b_{m1+2}, at most S + 2 vectors
-  char *ring = base + ((size_t)nslot + S + 1) * vecp;
+  char *ring = base + ((size_t)nslot + (keep ? 0 : S + 1)) * vecp;
   auto bv = [&](int k) -> void * { return ring + (size_t)(k % R) * vecp; };
   const double kdiag = 4.0 - p->m_W;
   const double *al = p->alpha.data();
@@ -2345,9 +2408,13 @@ int ovl_sign_force(const ovl_gauge *g, const ovl_poly *p, void *G, const void *c
     // b_m = alpha_m chi + 2 X b_{m+1} - b_{m+2} for m = m1 .. max(m0, 1) (descending; b_{m1+1}
     // and b_{m1+2} come from the segment above or the start values).  The two recurrences are
     // independent, so their steps run as twins, one launch per pair of steps.
-    HIP_TRY(hipMemcpyAsync(seg(0), ck(m0), vec, hipMemcpyDeviceToDevice, s));
-    if (m1 >= m0 + 1) HIP_TRY(hipMemcpyAsync(seg(1), ck(m0 + 1), vec, hipMemcpyDeviceToDevice, s));
     int mt = m0 + 2, mb = m1;
+    if (keep) {
+      mt = m1 + 1;  // t_{m0} .. t_{m1} are there (consecutive slots)
+    } else {
+      HIP_TRY(hipMemcpyAsync(seg(0), ck(m0), vec, hipMemcpyDeviceToDevice, s));
+      if (m1 >= m0 + 1) HIP_TRY(hipMemcpyAsync(seg(1), ck(m0 + 1), vec, hipMemcpyDeviceToDevice, s));
+    }
     const int mb_end = std::max(m0, 1);
     while (mt <= m1 || mb >= mb_end) {
       // b_{N-1} has no b_{N+1} term: it runs alone (the twins share the w coefficient)
@@ -2376,7 +2443,8 @@ int ovl_sign_force(const ovl_gauge *g, const ovl_poly *p, void *G, const void *c
     const double cf = (m0 == 0 ? 1.0 : 2.0) / p->lmax;
     const int in_mode = j == nseg - 1 ? 0 : 1;
     const int out_mode = j == 0 ? 1 : 0;
-    if ((rc = launch_vjp(prec, g, G, G64, bv(m0 + 1), bv(m0 + 1 + len0), 1, seg(0), seg(len0),
+    char *tb = (char *)(keep ? ck(m0) : seg(0));
+    if ((rc = launch_vjp(prec, g, G, G64, bv(m0 + 1), bv(m0 + 1 + len0), 1, tb, tb + len0 * vecp,
                          vecp, len0, len, cf, 2.0 / p->lmax, in_mode, out_mode, s)))
       return rc;
   }
