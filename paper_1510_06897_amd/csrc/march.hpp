@@ -351,10 +351,12 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
       for (int i = 0; i < 12; ++i) {
         const cx<C> v0 = i < 6 ? u[i / 3][i % 3] : d[i / 3 - 2][i % 3];
         const cx<C> xv = i < 6 ? v0 : mk<C>(s5 * v0.re, s5 * v0.im);
-        cx<C> yv = mk<C>(kd * xv.re + kh * acc[i].re, kd * xv.im + kh * acc[i].im);
+        // the roundings of the direction-split kernels, spelled out
+        cx<C> yv = mk<C>(fma(kd, xv.re, kh * acc[i].re), fma(kd, xv.im, kh * acc[i].im));
         if (i >= 6) yv = mk<C>(sy * yv.re, sy * yv.im);
-        yv = yv + scale(sv[i], i < 6 ? al : ah);
-        acc[i] = yv + scale(wv[i], tw);
+        const C ai = i < 6 ? al : ah;
+        yv = mk<C>(fma(ai, sv[i].re, yv.re), fma(ai, sv[i].im, yv.im));
+        acc[i] = mk<C>(fma(tw, wv[i].re, yv.re), fma(tw, wv[i].im, yv.im));
       }
 #pragma unroll
       for (int i = 0; i < 12; ++i) bio<SE, C>::st(o, vo, so + i * cs, acc[i]);
