@@ -288,11 +288,6 @@ struct TuneKey {
 std::mutex g_tune_mu;
 std::map<TuneKey, LaunchCfg> g_tuned;
 
-LaunchCfg default_cfg(int64_t work, int prec = P_F64) {
-  const int spb = (prec == P_F32 && work >= 512 * 1024) ? 128 : launch_spb(work);
-  return LaunchCfg{spb, 1, 1, 1};
-}
-
 // Tile of the t-marching form for a lattice: whole x lines, ty x tz in (y, z) dividing the extents,
 // n = Lx ty tz sites in whole waves, at most kMarchThreads, and no more face sites than that; the
 // links' t slices must be whole 64-site blocks.  Among the tiles the one with the fewest face sites
@@ -336,6 +331,16 @@ int64_t march_slices(const StepItem &it) {
   return n ? (int64_t)it.g.V / n * it.nrhs : 0;
 }
 
+// bytes of the three vectors and the links of a launch's steps
+int64_t step_set_bytes(int prec, const StepItem *items, int n) {
+  const int link = prec == P_F64 ? 16 : prec == P_F32 ? 8 : 4;
+  int64_t bytes = 0;
+  for (int i = 0; i < n; ++i)
+    bytes += 3 * 12 * (int64_t)items[i].g.V * items[i].nrhs * (prec == P_F64 ? 16 : 8) +
+             (int64_t)36 * items[i].g.V * link;
+  return bytes;
+}
+
 // Where the t-marching form is the default: the step's three vectors and the links exceed the 256 MB
 // last-level cache, and most sites lie in tiles of kMarchThreads sites.  Measured, one fused step in
 // the default form / t-marching, us: 16^3 x 32 FP64 3 vectors (302 MB with the links) 79.8 / 79.7,
@@ -345,14 +350,9 @@ int64_t march_slices(const StepItem &it) {
 // vectors: 18.8 / 29.0), and 192-site tiles leave a quarter of the threads idle (12^3 x 24, 24 FP32
 // vectors: 93 / 103).
 bool march_pays(int prec, const StepItem *items, int n) {
-  int64_t bytes = 0, sites = 0, full = 0;
-  for (int i = 0; i < n; ++i) {
-    const int64_t w = (int64_t)items[i].g.V * items[i].nrhs;
-    const int link = prec == P_F64 ? 16 : prec == P_F32 ? 8 : 4;
-    bytes += 3 * 12 * w * (prec == P_F64 ? 16 : 8) + (int64_t)36 * items[i].g.V * link;
-    sites += w;
-  }
-  if (bytes < (int64_t)256 << 20) return false;
+  int64_t sites = 0, full = 0;
+  for (int i = 0; i < n; ++i) sites += (int64_t)items[i].g.V * items[i].nrhs;
+  if (step_set_bytes(prec, items, n) < (int64_t)256 << 20) return false;
   for (int i = 0; i < n; ++i) {
     int ty, tz;
     const int t = march_tile(items[i].g, ty, tz);
@@ -360,6 +360,17 @@ bool march_pays(int prec, const StepItem *items, int n) {
     if (t == kMarchThreads) full += (int64_t)items[i].g.V * items[i].nrhs;
   }
   return 2 * full >= sites;
+}
+
+// Launch form without a measured one.  16-bit links run in memory order while the step's vectors and
+// links fit the last-level cache with room: the tiles save L2 misses that cost little there and lose
+// on their shorter XCD ranges (tiles / memory order, us per step: 16^3 x 32 57 MB 15.8 / 15.0, 2 vectors
+// 94 MB 27.5 / 25.9, 20^3 x 32 110 MB 28.1 / 26.5; 16^3 x 32 3 vectors 132 MB 35.5 / 36.3, 24^3 x 48
+// 285 MB 66.1 / 69.0).  FP32 is even there (16^3 x 32 18.6 / 18.5), FP64 faster in tiles (32.6 / 35.5).
+LaunchCfg default_cfg(int64_t work, int prec, const StepItem *items, int n) {
+  const int spb = (prec == P_F32 && work >= 512 * 1024) ? 128 : launch_spb(work);
+  const bool tiles = prec != P_F32_BF16 || step_set_bytes(prec, items, n) >= (int64_t)120 << 20;
+  return LaunchCfg{spb, tiles, 1, 1};
 }
 
 TuneKey tune_key(int prec, const StepItem *items, int n) {
@@ -379,17 +390,9 @@ LaunchCfg lookup_cfg(int prec, const StepItem *items, int n, int64_t work) {
   auto it = g_tuned.find(k);
   if (it != g_tuned.end()) {
     if (it->second.tiles != kMarch || march_ok(items, n)) return it->second;
-    return default_cfg(work, prec);
+    return default_cfg(work, prec, items, n);
   }
-  return march_pays(prec, items, n) ? LaunchCfg{64, kMarch, 1, 1} : default_cfg(work, prec);
-}
-LaunchCfg lookup_cfg(const Geom &g, int prec, int nrhs, int64_t work, int r12) {
-  StepItem it;
-  std::memset(&it, 0, sizeof(it));
-  it.g = g;
-  it.nrhs = nrhs;
-  it.r12 = r12;
-  return lookup_cfg(prec, &it, 1, work);
+  return march_pays(prec, items, n) ? LaunchCfg{64, kMarch, 1, 1} : default_cfg(work, prec, items, n);
 }
 
 // two sites per lane need FP32 spinors, an even Lx (pairs never straddle an x line) and 16-byte
@@ -428,8 +431,8 @@ bool slab_ok(const Geom &g, int spb, Prec prec) {
   const int bytes = prec == P_F64 ? slab_lds_bytes<double>(spb, g.L[0]) : slab_lds_bytes<float>(spb, g.L[0]);
   return bytes <= 160 * 1024 - 512;
 }
-LaunchCfg fit_slab(LaunchCfg c, const Geom &g, Prec prec, int64_t work, bool pairs) {
-  if (c.tiles == 2 && !slab_ok(g, c.spb, prec)) return fit_cfg(default_cfg(work, prec), pairs);
+LaunchCfg fit_slab(LaunchCfg c, const StepItem &it, Prec prec, int64_t work, bool pairs) {
+  if (c.tiles == 2 && !slab_ok(it.g, c.spb, prec)) return fit_cfg(default_cfg(work, prec, &it, 1), pairs);
   return c;
 }
 
@@ -656,7 +659,7 @@ int dispatch_single(Prec prec, StepArgs<false> &p, hipStream_t s) {
   const int64_t work = items_work(&p.item, 1);
   const bool pairs = pairs_ok(prec, &p.item, 1);
   const LaunchCfg cfg = fit_slab(
-      fit_cfg(lookup_cfg(p.item.g, prec, p.item.nrhs, work, p.item.r12), pairs), p.item.g, prec,
+      fit_cfg(lookup_cfg((int)prec, &p.item, 1, work), pairs), p.item, prec,
       work, pairs);
   return dispatch_cfg(prec, p, cfg, s);
 }
@@ -901,8 +904,8 @@ LaunchCfg sign_cfg(const SignJob *jobs, int nj, Prec prec) {
   StepItem key_items[kMaxBatch];
   for (int j = 0; j < nj; ++j) fill_item(key_items[j], jobs[j].g, jobs[j].nrhs);
   LaunchCfg cfg = fit_cfg(lookup_cfg((int)prec, key_items, nj, work), pairs);
-  if (TABLE) return cfg.tiles == 2 ? fit_cfg(default_cfg(work, prec), pairs) : cfg;
-  return fit_slab(cfg, jobs[0].g->g, prec, work, pairs);
+  if (TABLE) return cfg.tiles == 2 ? fit_cfg(default_cfg(work, prec, key_items, nj), pairs) : cfg;
+  return fit_slab(cfg, key_items[0], prec, work, pairs);
 }
 
 template <bool TABLE>
@@ -3152,8 +3155,9 @@ int ovl_launch_config(const ovl_gauge *g, int nrhs, int spin_dt, int cfg_out[3])
   // vectors are taken as 16-byte aligned (torch allocations are)
   const int64_t work = (int64_t)g->g.V * nrhs;
   const bool pairs = prec != P_F64 && g->g.L[0] % 2 == 0;
-  const LaunchCfg c = fit_slab(fit_cfg(lookup_cfg(g->g, prec, nrhs, work, g->r12), pairs), g->g,
-                               prec, work, pairs);
+  StepItem it;
+  fill_item(it, g, nrhs);
+  const LaunchCfg c = fit_slab(fit_cfg(lookup_cfg((int)prec, &it, 1, work), pairs), it, prec, work, pairs);
   cfg_out[0] = c.spb;
   cfg_out[1] = c.tiles;
   cfg_out[2] = c.remap;
