@@ -952,7 +952,7 @@ __global__ void __launch_bounds__(kBlock)
 // data: v_mfma_f64_16x16x4f64, FP64 throughout.  The four waves of a workgroup are added in FP64 in
 // fixed order and pass 2 sums the workgroups in FP64.
 // Bound by memory: the bytes are the basis and the right-hand sides once each (24 FP64 vectors and 12
-// right-hand sides of 16^3 x 32: 906 MB in 221 us, 4.1 TB/s; the VALU kernel, which reads the basis
+// right-hand sides of 16^3 x 32: 906 MB in 228 us, 4.0 TB/s; the VALU kernel, which reads the basis
 // once per right-hand side, takes 1.35 ms).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -1027,6 +1027,13 @@ __global__ void __launch_bounds__(256)
     for (int y = 0; y < TR; ++y)
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc64[x][y][q] = 0.0;
+  double low[F32 ? 1 : TE][TR][4];  // FP64: the roundings of the running sums (two-sum)
+#pragma unroll
+  for (int x = 0; x < (F32 ? 1 : TE); ++x)
+#pragma unroll
+    for (int y = 0; y < TR; ++y)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) low[x][y][q] = 0.0;
   // Each step covers 4 waves x 4 lane groups x kMfmaT reals.  The loop bound is uniform over the
   // wave: an MFMA reads its operands from every lane regardless of the execution mask, so no lane
   // may leave the loop early; positions past the chunk (a multiple of kMfmaT, like K) read the
@@ -1060,8 +1067,10 @@ __global__ void __launch_bounds__(256)
     for (int x = 0; x < TE; ++x)
 #pragma unroll
       for (int y = 0; y < TR; ++y) {
-        // the matrix core sums the step's 16 products per lane group; the running sum is FP64 and
-        // separate (one chain of all the chunk's FP64 products measured 1.6x the rounding error)
+        // the matrix core sums the step's 16 products (FP64: 8 and 8); the running sums are FP64 and
+        // separate.  FP64 error against extended precision over 12 vectors and 12 right-hand sides of
+        // 16^3 x 32: one chain of the chunk's products 8.5e-16, one running sum 2.8e-16, with
+        // its roundings carried along 2.2e-16 (10 us of 220), the VALU kernel 2.6e-16.
         if constexpr (F32) {
           f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1070,14 +1079,30 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
           for (int q = 0; q < 4; ++q) acc64[x][y][q] += (double)acc[q];
         } else {
-          f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+          f64x4 lo = {0.0, 0.0, 0.0, 0.0}, hi = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-          for (int t = 0; t < kMfmaT; ++t)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x][t], b[y][t], acc, 0, 0, 0);
+          for (int t = 0; t < kMfmaT / 2; ++t) {
+            lo = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x][t], b[y][t], lo, 0, 0, 0);
+            hi = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x][t + kMfmaT / 2], b[y][t + kMfmaT / 2], hi, 0, 0, 0);
+          }
 #pragma unroll
-          for (int q = 0; q < 4; ++q) acc64[x][y][q] += acc[q];
+          for (int q = 0; q < 4; ++q) {
+            const double v = lo[q] + hi[q], s = acc64[x][y][q];
+            const double n = s + v, d = n - s;
+            low[x][y][q] += (s - (n - d)) + (v - d);
+            acc64[x][y][q] = n;
+          }
         }
       }
+  }
+  if constexpr (!F32) {
+#pragma unroll
+    for (int x = 0; x < TE; ++x)
+#pragma unroll
+      for (int y = 0; y < TR; ++y)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)  // (an infinite sum has no rounding to add: inf - inf is NaN)
+          if (low[x][y][q] == low[x][y][q]) acc64[x][y][q] += low[x][y][q];
   }
 #pragma unroll
   for (int x = 0; x < TE; ++x)
@@ -1105,16 +1130,22 @@ __global__ void __launch_bounds__(256)
 }
 
 // pass 2: c[r][i] = sum_b partial[b][r][i]; one wave per output, lane l sums blocks l, l + 64, ...
-// and the wave adds the lanes in a fixed butterfly (deterministic)
+// (eight at a time: 2048 partials in one chain rounded more than the products) and the wave adds the
+// lanes in a fixed butterfly (deterministic)
 __global__ void __launch_bounds__(64)
     project_reduce_kernel(const double2 *__restrict__ partial, int nblk, int count,
                           double2 *__restrict__ c) {
   const int k = blockIdx.x;
   double re = 0.0, im = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += 64) {
-    const double2 v = partial[(int64_t)b * count + k];
-    re += v.x;
-    im += v.y;
+  for (int b0 = threadIdx.x; b0 < nblk; b0 += 512) {
+    double sre = 0.0, sim = 0.0;
+    for (int b = b0; b < b0 + 512 && b < nblk; b += 64) {
+      const double2 v = partial[(int64_t)b * count + k];
+      sre += v.x;
+      sim += v.y;
+    }
+    re += sre;
+    im += sim;
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
