@@ -185,6 +185,8 @@ def kernel_name(cfg, store, two_row, table=True):
                  "bf16": ("float", "float2", "bf16c")}[store]
     if order == 2:
         return f"step_slab_kernel<{c},{se},{le},NW={spb // 64},TABLE={int(table)},R12={int(two_row)}>"
+    if order == 3:
+        return f"march_kernel<{c},{se},{le},TABLE={int(table)},R12={int(two_row)}>"
     if spb == 128:
         return f"step2_kernel<{le},64,TABLE={int(table)},R12={int(two_row)}>"
     nq = 8 if spb == 8 else 4

@@ -14,9 +14,8 @@
 // through raw buffer resources (lane offset site * 16 bytes, element offset in a scalar register),
 // so a field must span less than 4 GiB.  A thread owns one link
 // (site, mu); the workgroup's 256 threads share mu, so the path loops below are uniform over a
-// wave.  exp(M) is a Taylor series after scaling M to norm <= 1/2, followed by squaring; the
-// derivative of exp comes from the same series for the Frechet derivative, carried along the
-// squarings.
+// wave.  exp(M) is a Taylor series on the Cayley-Hamilton coefficients after scaling M to norm
+// <= 1/2, followed by squaring; the Frechet derivative of exp comes from the same series.
 #pragma once
 
 #include "common.hpp"
