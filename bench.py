@@ -809,7 +809,7 @@ def main():
     # the counters of the configuration this run's tuner chose (the summary holds the forms the
     # tuner picks between)
     rl = roofline(kernel_name(bt["config"], "f32", True), batch_bytes, bt["kernel_ms"],
-                  bt["kernel_launches"], tag="step2_kernel_sign_batch", cfg=bt["config"])
+                  bt["kernel_launches"], tag="march_kernel_sign_batch", cfg=bt["config"])
     rl["bytes_model"] = ("per step: every lattice's links once (two rows, 192 B/site) + "
                          "3.5 FP32 spinor streams (96 B each) per site and right-hand side")
     if "bf16_24modes_16x16x16x32" in extra:
