@@ -82,6 +82,30 @@ __device__ __forceinline__ void load_link_off(rsrc_t U, uint32_t ls, uint32_t vo
 }
 
 constexpr int kMarchThreads = 256;  // most sites of a tile, and most face sites
+
+// Tile of the t-marching form for a lattice: whole x lines, ty x tz in (y, z) dividing the extents,
+// n = Lx ty tz sites in whole waves, at most kMarchThreads, and no more face sites than that (a thread
+// stages at most one tile site and one face site; the faces may outnumber the tile's sites, as for
+// 32 x 2 x 2 with 128 and 256); the links' t slices must be whole 64-site blocks.  Among the tiles the
+// one with the fewest face sites per site wins.  Returns n (0: none fits).
+inline int march_tile(const Geom &g, int &ty, int &tz) {
+  ty = tz = 0;
+  if ((int64_t)g.L[0] * g.L[1] * g.L[2] % 64 || g.L[0] > kMarchThreads) return 0;
+  int64_t best = 0, bh = 0;
+  for (int a = 1; a <= g.L[1] && g.L[0] * a <= kMarchThreads; ++a)
+    for (int b = 1; b <= g.L[2] && g.L[0] * a * b <= kMarchThreads; ++b) {
+      const int64_t n = (int64_t)g.L[0] * a * b;
+      if (g.L[1] % a || g.L[2] % b || n % 64) continue;
+      const int64_t h = (a < g.L[1] ? 2 * g.L[0] * b : 0) + (b < g.L[2] ? 2 * g.L[0] * a : 0);
+      if (h > kMarchThreads || (best && h * best >= bh * n)) continue;
+      best = n;
+      bh = h;
+      ty = a;
+      tz = b;
+    }
+  return (int)best;
+}
+
 // LDS bytes of a workgroup: 12 components of the tile and its faces
 template <class C>
 __host__ __device__ constexpr int march_lds_bytes() {
@@ -94,8 +118,12 @@ struct MarchPlace {
   int n, nh;                    // tile sites, face sites
   int y0, z0;                   // corner of the tile
   int hy, hz;                   // sites of one y face, one z face (0: the tile wraps there)
+  // thread tid stages (and computes) tile site tid, and stages face site tid: each by its own bound,
+  // as either count may be the larger
+  __host__ __device__ bool tile_lane(int tid) const { return tid < n; }
+  __host__ __device__ bool face_lane(int tid) const { return tid < nh; }
 };
-__device__ __forceinline__ MarchPlace march_place(const StepItem &I, const Ext4 &ex, int lb) {
+__host__ __device__ __forceinline__ MarchPlace march_place(const StepItem &I, const Ext4 &ex, int lb) {
   MarchPlace p;
   const int ty = I.mty, tz = I.mtz, nrhs = I.nrhs;
   const int nty = ex.ly / ty, ntile = nty * (ex.lz / tz);
@@ -121,7 +149,7 @@ __device__ __forceinline__ MarchPlace march_place(const StepItem &I, const Ext4 
   return p;
 }
 // (x, y, z) site index of staged site j: the tile's sites, then the faces y + ty, y - 1, z + tz, z - 1
-__device__ __forceinline__ int march_staged(const MarchPlace &p, const StepItem &I, const Ext4 &ex,
+__host__ __device__ __forceinline__ int march_staged(const MarchPlace &p, const StepItem &I, const Ext4 &ex,
                                             int j) {
   int xx, yy, zz;
   if (j < p.n) {
@@ -151,7 +179,7 @@ struct MarchSite {
   int s3, xm3, ym3, zm3;
   int jxp, jxm, jyp, jym, jzp, jzm;
 };
-__device__ __forceinline__ MarchSite march_site(const MarchPlace &p, const StepItem &I,
+__host__ __device__ __forceinline__ MarchSite march_site(const MarchPlace &p, const StepItem &I,
                                                 const Ext4 &ex, int sj) {
   MarchSite m;
   const int ty = I.mty, tz = I.mtz, n = p.n;
@@ -189,7 +217,7 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
   const MarchPlace mp = march_place(I, ex, gb - I.mblk0);
   const int r = mp.r, t0 = mp.t0, t1 = mp.t1, n = mp.n, V3 = ex.st;
   const int tid = threadIdx.x;
-  const bool active = tid < n, hactive = tid < mp.nh;
+  const bool active = mp.tile_lane(tid), hactive = mp.face_lane(tid);
   const int sj = active ? tid : 0;
   const MarchSite ms = march_site(mp, I, ex, sj);
   const int jxp = ms.jxp, jxm = ms.jxm, jyp = ms.jyp, jym = ms.jym, jzp = ms.jzp, jzm = ms.jzm;
@@ -269,6 +297,9 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
     half_project<3, -1>(pu, pd, s5, h);
     half_mul<true>(k0, h, bt);
     links4(t0);
+  } else if (hactive) {  // a wave with faces only
+    load12(vh, t0, hu, hd);
+    put12(n + tid, hu, hd);
   }
   __syncthreads();
   using I0 = std::integral_constant<int, 0>;
@@ -360,14 +391,16 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
       }
 #pragma unroll
       for (int i = 0; i < 12; ++i) bio<SE, C>::st(o, vo, so + i * cs, acc[i]);
+    } else if (hactive && t + 1 < t1) {
+      load12(vh, t + 1, hu, hd);
     }
     if (t + 1 < t1) {
       __syncthreads();
       if (active) {
         links4(t + 1);
         put12(sj, pu, pd);
-        if (hactive) put12(n + tid, hu, hd);
       }
+      if (hactive) put12(n + tid, hu, hd);
       __syncthreads();
     }
   }

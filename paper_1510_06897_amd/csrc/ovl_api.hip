@@ -288,27 +288,6 @@ struct TuneKey {
 std::mutex g_tune_mu;
 std::map<TuneKey, LaunchCfg> g_tuned;
 
-// Tile of the t-marching form for a lattice: whole x lines, ty x tz in (y, z) dividing the extents,
-// n = Lx ty tz sites in whole waves, at most kMarchThreads, and no more face sites than that; the
-// links' t slices must be whole 64-site blocks.  Among the tiles the one with the fewest face sites
-// per site wins.  Returns n (0: none fits).
-int march_tile(const Geom &g, int &ty, int &tz) {
-  ty = tz = 0;
-  if ((int64_t)g.L[0] * g.L[1] * g.L[2] % 64 || g.L[0] > kMarchThreads) return 0;
-  int64_t best = 0, bh = 0;
-  for (int a = 1; a <= g.L[1] && g.L[0] * a <= kMarchThreads; ++a)
-    for (int b = 1; b <= g.L[2] && g.L[0] * a * b <= kMarchThreads; ++b) {
-      const int64_t n = (int64_t)g.L[0] * a * b;
-      if (g.L[1] % a || g.L[2] % b || n % 64) continue;
-      const int64_t h = (a < g.L[1] ? 2 * g.L[0] * b : 0) + (b < g.L[2] ? 2 * g.L[0] * a : 0);
-      if (h > kMarchThreads || (best && h * best >= bh * n)) continue;
-      best = n;
-      bh = h;
-      ty = a;
-      tz = b;
-    }
-  return (int)best;
-}
 bool march_ok(const StepItem *items, int n) {
   int ty, tz;
   for (int i = 0; i < n; ++i)
