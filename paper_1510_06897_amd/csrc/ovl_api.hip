@@ -1292,8 +1292,7 @@ int ovl_gauge_create(ovl_gauge **out, const int32_t dims[4], const void *U_dev, 
 int ovl_gauge_destroy(ovl_gauge *g) {
   g_err[0] = 0;
   if (!g) return OVL_OK;
-  (void)hipDeviceSynchronize();
-  block_cache().give(g->mem, nullptr);
+  block_cache().retire(g->mem);
   delete g;
   return OVL_OK;
 }

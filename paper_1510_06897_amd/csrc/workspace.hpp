@@ -26,7 +26,8 @@ constexpr uint64_t kKeepReturns = 1024;
 struct Block {
   void *p = nullptr;
   size_t bytes = 0;
-  hipEvent_t evt = nullptr;  // recorded at the last return
+  hipEvent_t evt = nullptr;  // recorded at the last return, unless the device was idle then
+  bool pending = false;      // evt may still have to be waited for
   int dev = -1;
   uint64_t stamp = 0;
 };
@@ -53,7 +54,7 @@ class BlockCache {
       }
     }
     if (out.p) {
-      e = hipStreamWaitEvent(s, out.evt, 0);
+      e = out.pending ? hipStreamWaitEvent(s, out.evt, 0) : hipSuccess;
       if (e != hipSuccess) drop(out);
       return e;
     }
@@ -79,6 +80,31 @@ class BlockCache {
       drop(b);
       return;
     }
+    b.pending = true;
+    keep(b);
+  }
+
+  // hand back the block of a handle that ends; its work may be on any stream of the block's device, so
+  // the device has to be idle.  Where that wait is refused (some stream is captured) the block is freed
+  // instead: hipFree waits by itself.
+  void retire(Block &b) {
+    if (!b.p) return;
+    const int dev = b.dev;
+    int cur = dev;
+    (void)hipGetDevice(&cur);
+    if (cur != dev) (void)hipSetDevice(dev);
+    if (hipDeviceSynchronize() == hipSuccess) {
+      b.pending = false;
+      keep(b);
+    } else {
+      (void)hipGetLastError();
+      drop(b);
+    }
+    if (cur != dev) (void)hipSetDevice(cur);
+  }
+
+ private:
+  void keep(Block &b) {
     const int dev = b.dev;
     {
       std::lock_guard<std::mutex> lk(mu_);
@@ -88,8 +114,6 @@ class BlockCache {
     b = Block();
     trim(dev, limit(dev));
   }
-
- private:
   // Allocation and release are not stream operations: they leave a capture of another stream alone.
   struct Relaxed {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;

@@ -1,0 +1,70 @@
+// Host checks of the memory kept between calls (csrc/workspace.hpp) against the stand-in runtime.
+#include <cstdio>
+#include <cstring>
+
+#include "../../paper_1510_06897_amd/csrc/workspace.hpp"
+
+using namespace ovl;
+
+static int failed = 0;
+#define CHECK(c)                                            \
+  do {                                                      \
+    if (!(c)) {                                             \
+      std::printf("line %d: %s\n", __LINE__, #c);           \
+      ++failed;                                             \
+    }                                                       \
+  } while (0)
+
+constexpr size_t MB = (size_t)1 << 20;
+
+// a handle that ends while work on some stream still reads its memory
+static void destroy_refused() {
+  ihipStream s;
+  fake().streams.insert(&s);
+  Block b;
+  CHECK(block_cache().take(64 * MB, &s, b) == hipSuccess);
+  void *const p = b.p;
+  ++s.issued;  // a kernel that reads the block, on a stream the null stream does not wait for
+  fake().sync_refused = true;
+  block_cache().retire(b);
+  fake().sync_refused = false;
+  CHECK(b.p == nullptr);
+  CHECK(fake().live.count(p) == 0);  // hipFree, which waits: not kept for another user
+  Block c;
+  CHECK(block_cache().take(64 * MB, nullptr, c) == hipSuccess && c.p != p);
+  // and one that ends as it should: kept, no wait left for its next user
+  void *const q = c.p;
+  block_cache().retire(c);
+  const int waits = fake().waits;
+  CHECK(block_cache().take(64 * MB, &s, c) == hipSuccess && c.p == q && fake().waits == waits);
+  block_cache().retire(c);
+  fake().streams.erase(&s);
+}
+
+// a handle of device 1 that ends while device 0 is current: the wait is for device 1
+static void destroy_elsewhere() {
+  ihipStream s;
+  s.device = 1;
+  fake().streams.insert(&s);
+  fake().device = 1;
+  Block b;
+  CHECK(block_cache().take(64 * MB, &s, b) == hipSuccess);
+  ++s.issued;
+  fake().device = 0;
+  block_cache().retire(b);
+  CHECK(fake().device == 0 && s.ended == s.issued);
+  fake().streams.erase(&s);
+}
+
+int main(int argc, char **argv) {
+  const char *what = argc > 1 ? argv[1] : "";
+  if (!std::strcmp(what, "destroy")) {
+    destroy_refused();
+    destroy_elsewhere();
+  } else {
+    std::printf("no check named '%s'\n", what);
+    return 2;
+  }
+  std::printf("%d failed\n", failed);
+  return failed != 0;
+}
