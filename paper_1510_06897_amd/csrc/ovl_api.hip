@@ -1255,7 +1255,7 @@ int ovl_gauge_create(ovl_gauge **out, const int32_t dims[4], const void *U_dev, 
   hipError_t e = hipGetDevice(&g->device);
   const int64_t n = (int64_t)36 * geo.V;
   const size_t lbytes = ((size_t)nlink * elem_bytes(store_dt) + 255) / 256 * 256;
-  if (e == hipSuccess) e = block_cache().take(lbytes + 256, s, g->mem);
+  if (e == hipSuccess) e = block_cache().take_handle(lbytes + 256, s, g->mem);
   if (e == hipSuccess) {
     g->links = g->mem.p;
     g->flags = (uint32_t *)((char *)g->mem.p + lbytes);

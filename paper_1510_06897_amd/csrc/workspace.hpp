@@ -26,7 +26,7 @@ constexpr uint64_t kKeepReturns = 1024;
 struct Block {
   void *p = nullptr;
   size_t bytes = 0;
-  hipEvent_t evt = nullptr;  // recorded at the last return, unless the device was idle then
+  hipEvent_t evt = nullptr;  // (null: never kept) recorded at the last return, unless the device was idle then
   bool pending = false;      // evt may still have to be waited for
   int dev = -1;
   uint64_t stamp = 0;
@@ -72,10 +72,24 @@ class BlockCache {
     return e;
   }
 
+  // Memory of a handle made on stream s.  Below kKeepBlock it is allocated and freed as it is needed, and
+  // so it is while s is captured: a kept block would make the capture wait on an event outside it.
+  hipError_t take_handle(size_t bytes, hipStream_t s, Block &out) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(s, &cap);
+    if (e != hipSuccess) return e;
+    if (bytes >= kKeepBlock && cap == hipStreamCaptureStatusNone) return take(bytes, s, out);
+    e = hipGetDevice(&out.dev);
+    if (e == hipSuccess) e = hipMalloc(&out.p, bytes);
+    if (e != hipSuccess) out = Block();
+    else out.bytes = bytes;
+    return e;
+  }
+
   // hand a block back; s: the stream its last user worked on (other users' work has ended)
   void give(Block &b, hipStream_t s) {
     if (!b.p) return;
-    if (hipEventRecord(b.evt, s) != hipSuccess) {
+    if (!b.evt || hipEventRecord(b.evt, s) != hipSuccess) {
       (void)hipGetLastError();
       drop(b);
       return;
@@ -85,15 +99,15 @@ class BlockCache {
   }
 
   // hand back the block of a handle that ends; its work may be on any stream of the block's device, so
-  // the device has to be idle.  Where that wait is refused (some stream is captured) the block is freed
-  // instead: hipFree waits by itself.
+  // the device has to be idle.  Where that wait is refused (some stream is captured), and for a block that
+  // is never kept, the block is freed instead: hipFree waits by itself.
   void retire(Block &b) {
     if (!b.p) return;
     const int dev = b.dev;
     int cur = dev;
     (void)hipGetDevice(&cur);
     if (cur != dev) (void)hipSetDevice(dev);
-    if (hipDeviceSynchronize() == hipSuccess) {
+    if (hipDeviceSynchronize() == hipSuccess && b.evt) {
       b.pending = false;
       keep(b);
     } else {

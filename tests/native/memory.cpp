@@ -56,11 +56,42 @@ static void destroy_elsewhere() {
   fake().streams.erase(&s);
 }
 
+// a handle made on a captured stream takes no kept block, whatever there is; nor does a small one
+static void create() {
+  Block b;
+  CHECK(block_cache().take_handle(64 * MB, nullptr, b) == hipSuccess && b.evt);
+  void *const kept = b.p;
+  block_cache().retire(b);
+  ihipStream s;
+  fake().streams.insert(&s);
+  s.capturing = true;
+  const int waits = fake().waits;
+  CHECK(block_cache().take_handle(64 * MB, &s, b) == hipSuccess && b.p != kept && fake().waits == waits);
+  CHECK(fake().live[b.p] == 64 * MB);
+  s.capturing = false;
+  void *const p = b.p;
+  block_cache().retire(b);
+  CHECK(fake().live.count(p) == 0);
+  CHECK(block_cache().take_handle(MB / 8, &s, b) == hipSuccess && fake().live[b.p] == MB / 8);
+  void *const q = b.p;
+  block_cache().retire(b);
+  CHECK(fake().live.count(q) == 0 && fake().live.count(kept) == 1);
+  // given back half made
+  CHECK(block_cache().take_handle(MB / 8, &s, b) == hipSuccess);
+  block_cache().give(b, &s);
+  CHECK(b.p == nullptr && fake().live.size() == 1);
+  CHECK(block_cache().take_handle(64 * MB, &s, b) == hipSuccess && b.p == kept);
+  block_cache().give(b, &s);
+  fake().streams.erase(&s);
+}
+
 int main(int argc, char **argv) {
   const char *what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "destroy")) {
     destroy_refused();
     destroy_elsewhere();
+  } else if (!std::strcmp(what, "create")) {
+    create();
   } else {
     std::printf("no check named '%s'\n", what);
     return 2;
