@@ -436,6 +436,14 @@ int ovl_status_flags(const ovl_gauge *g, uint32_t *flags, int clear);
  * Results are bitwise identical either way. */
 int ovl_graph_enable(int on);
 
+/* Gives the device memory that the library keeps between calls back to the current device.  Kept are
+ * work space and link fields of 16 MB and more, up to an eighth of the device's memory (the default
+ * ovl_sign_force alone can leave a tenth), and the free memory of the device's stream-ordered pool.
+ * The library does this by itself when one of its allocations runs out of memory; a program whose other
+ * allocator (torch's, say) needs the memory calls this.  Synchronises the device; live handles and
+ * results are not touched.  Errors: EHIP (as when a stream is being captured). */
+int ovl_memory_release(void);
+
 /* Kernel timing (measurement support).  When enabled, every sign evaluation (sign, overlap,
  * batched sign) records one HIP event on its stream before its first plain recurrence step and
  * one after its last (the steps k = N-1 .. 1 are consecutive launches of the fused Chebyshev

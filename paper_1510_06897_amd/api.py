@@ -449,6 +449,13 @@ def graph_enable(on: bool = True):
     call("ovl_graph_enable", 1 if on else 0)
 
 
+def memory_release():
+    """Give the device memory the library keeps between calls back to the current device (work space and
+    link fields of 16 MB and more, up to an eighth of the device's memory).  torch's allocator cannot reach
+    that memory: call this when torch needs it."""
+    call("ovl_memory_release")
+
+
 def timing_enable(on: bool = True):
     call("ovl_timing_enable", 1 if on else 0)
 

@@ -93,16 +93,23 @@ int scratch_alloc(Scratch &sc, size_t bytes, hipStream_t s) {
     if (rc != OVL_OK) return rc;
   }
   sc.s = s;
-  if (bytes >= kKeepBlock) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing(s, &cap));
-    if (cap == hipStreamCaptureStatusNone) {
-      HIP_TRY(block_cache().take(bytes, s, sc.block));
-      sc.p = sc.block.p;
-      return OVL_OK;
+  auto from_pool = [&] { return hipMallocAsync(&sc.p, std::max<size_t>(bytes, 256), s); };
+  hipError_t e = hipSuccess;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (bytes >= kKeepBlock) HIP_TRY(hipStreamIsCapturing(s, &cap));
+  if (bytes >= kKeepBlock && cap == hipStreamCaptureStatusNone) {
+    e = block_cache().take(bytes, s, sc.block);
+    sc.p = sc.block.p;
+  } else {
+    e = from_pool();
+    // (a captured allocation happens at the replay: nothing to give back now)
+    if (e == hipErrorOutOfMemory && hipStreamIsCapturing(s, &cap) == hipSuccess &&
+        cap == hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      e = block_cache().with_room(from_pool);
     }
   }
-  HIP_TRY(hipMallocAsync(&sc.p, std::max<size_t>(bytes, 256), s));
+  HIP_TRY(e);
   return OVL_OK;
 }
 
@@ -836,7 +843,7 @@ GraphEntry *graph_entry(const GraphKey &key, size_t work_bytes) {
   }
   GraphEntry e;
   e.key = key;
-  if (hipMalloc(&e.work, work_bytes) != hipSuccess) {
+  if (block_cache().with_room([&] { return hipMalloc(&e.work, work_bytes); }) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
@@ -1446,8 +1453,11 @@ int ovl_defl_create(ovl_defl **out, const int32_t dims[4], const void *phi_dev, 
     return code;
   };
   const size_t wbytes = sizeof(double) * (size_t)n_ev * ovl_defl::kWSlots;
-  hipError_t e = hipMalloc((void **)&d->phi64, n * sizeof(double2));
-  if (e == hipSuccess) e = hipMalloc((void **)&d->w_dev, wbytes);
+  auto alloc = [](auto **p, size_t bytes) {
+    return block_cache().with_room([&] { return hipMalloc((void **)p, bytes); });
+  };
+  hipError_t e = alloc(&d->phi64, n * sizeof(double2));
+  if (e == hipSuccess) e = alloc(&d->w_dev, wbytes);
   if (e == hipSuccess) e = hipHostMalloc((void **)&d->w_pin, wbytes, hipHostMallocDefault);
   for (int k = 0; k < ovl_defl::kWSlots && e == hipSuccess; ++k)
     e = hipEventCreateWithFlags(&d->w_evt[k], hipEventDisableTiming);
@@ -1503,7 +1513,7 @@ int ovl_defl_create(ovl_defl **out, const int32_t dims[4], const void *phi_dev, 
   if (store_dt == OVL_F64) {
     d->phi_store = d->phi64;
   } else {
-    e = hipMalloc(&d->phi_store, n * sizeof(float2));
+    e = alloc(&d->phi_store, n * sizeof(float2));
     if (e == hipSuccess) {
       convert_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>((const double2 *)d->phi64,
                                                                  (float2 *)d->phi_store, n);
@@ -3164,6 +3174,13 @@ int ovl_status_flags(const ovl_gauge *g, uint32_t *flags, int clear) {
   HIP_TRY(hipDeviceSynchronize());
   HIP_TRY(hipMemcpy(flags, g->flags, sizeof(uint32_t), hipMemcpyDeviceToHost));
   if (clear) HIP_TRY(hipMemset(g->flags, 0, sizeof(uint32_t)));
+  return OVL_OK;
+}
+
+int ovl_memory_release(void) {
+  g_err[0] = 0;
+  HIP_TRY(hipDeviceSynchronize());
+  block_cache().release();
   return OVL_OK;
 }
 

@@ -7,8 +7,10 @@
 // Blocks of 16 MB and more are therefore kept here.  A block belongs to one user at a time; when it is
 // given back an event marks the work that still uses it, and its next user's stream waits for that
 // event, so blocks pass between streams and threads safely.  At most an eighth of the device's memory is
-// kept (least recently used freed first), a block that 1024 later returns did not need is freed, and all of
-// them are when an allocation fails.
+// kept (least recently used freed first), and a block that 1024 later returns did not need is freed.
+// Everything kept, and what the pool holds, goes back when any allocation of the library runs out of
+// memory (with_room) and when the program asks for it (release): other allocators of the process, torch's
+// among them, cannot reach it.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -61,12 +63,7 @@ class BlockCache {
     const Relaxed relaxed;
     out.bytes = (bytes + kGrain - 1) / kGrain * kGrain;
     out.dev = dev;
-    e = hipMalloc(&out.p, out.bytes);
-    if (e == hipErrorOutOfMemory) {
-      (void)hipGetLastError();
-      trim(dev, 0);
-      e = hipMalloc(&out.p, out.bytes);
-    }
+    e = with_room([&] { return hipMalloc(&out.p, out.bytes); });
     if (e == hipSuccess) e = hipEventCreateWithFlags(&out.evt, hipEventDisableTiming);
     if (e != hipSuccess) drop(out);
     return e;
@@ -80,10 +77,33 @@ class BlockCache {
     if (e != hipSuccess) return e;
     if (bytes >= kKeepBlock && cap == hipStreamCaptureStatusNone) return take(bytes, s, out);
     e = hipGetDevice(&out.dev);
-    if (e == hipSuccess) e = hipMalloc(&out.p, bytes);
+    if (e == hipSuccess) e = with_room([&] { return hipMalloc(&out.p, bytes); });
     if (e != hipSuccess) out = Block();
     else out.bytes = bytes;
     return e;
+  }
+
+  // Gives every kept block of the current device and the free memory of its stream-ordered pool back to
+  // the device.
+  void release() {
+    int dev = 0;
+    hipMemPool_t pool;
+    if (hipGetDevice(&dev) == hipSuccess) {
+      trim(dev, 0);
+      const Relaxed relaxed;
+      if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+    }
+    (void)hipGetLastError();
+  }
+
+  // alloc(), and once more with everything kept given back if the device was out of memory
+  template <class F>
+  hipError_t with_room(F alloc) {
+    const hipError_t e = alloc();
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    release();
+    return alloc();
   }
 
   // hand a block back; s: the stream its last user worked on (other users' work has ended)

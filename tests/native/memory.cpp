@@ -85,6 +85,63 @@ static void create() {
   fake().streams.erase(&s);
 }
 
+// every allocation of the library that runs out of memory gets what is kept, in blocks and in the pool
+static void room() {
+  Block b, c;
+  CHECK(block_cache().take(6000 * MB, nullptr, b) == hipSuccess);
+  block_cache().give(b, nullptr);
+  CHECK(fake().live.size() == 1);
+  fake().free -= 1000 * MB;  // freed into the pool, which keeps it
+  fake().pool_free = 1000 * MB;
+  size_t all = fake().total;
+  auto fill = [&](size_t left) {  // other allocators take the rest
+    void *p = nullptr;
+    CHECK(hipMalloc(&p, fake().free - left) == hipSuccess);
+    return p;
+  };
+  void *rest = fill(100 * MB), *p = nullptr;
+  // a deflation basis or a graph's vector, out of the kept block
+  CHECK(block_cache().with_room([&] { return hipMalloc(&p, 5000 * MB); }) == hipSuccess);
+  CHECK(fake().live.size() == 2 && fake().pool_free == 0);
+  (void)hipFree(p);
+  // work space out of the pool's free memory; a small one from the pool itself out of a kept block
+  fake().pool_free = 1000 * MB, fake().free -= 1000 * MB;
+  (void)hipFree(rest);
+  rest = fill(100 * MB);
+  CHECK(block_cache().take(1000 * MB, nullptr, c) == hipSuccess);
+  block_cache().give(c, nullptr);
+  void *rest2 = fill(0);
+  CHECK(block_cache().with_room([&] { return hipMallocAsync(&p, MB, nullptr); }) == hipSuccess);
+  (void)hipFreeAsync(p, nullptr);
+  // a handle's memory, kept or plain
+  for (size_t n : {MB, 64 * MB}) {
+    Block k, h;
+    CHECK(block_cache().take(500 * MB, nullptr, k) == hipSuccess);
+    block_cache().give(k, nullptr);
+    void *r = fill(0);
+    CHECK(block_cache().take_handle(n, nullptr, h) == hipSuccess);
+    block_cache().retire(h);
+    (void)hipFree(r);
+  }
+  // what cannot be had is an error, with nothing left behind
+  Block none;
+  CHECK(block_cache().take(2 * all, nullptr, none) == hipErrorOutOfMemory && !none.p && !none.evt);
+  CHECK(block_cache().take_handle(2 * all, nullptr, none) == hipErrorOutOfMemory && !none.p);
+  (void)hipFree(rest);
+  (void)hipFree(rest2);
+  // on request, and no more than an eighth of the device is kept without one
+  for (int i = 0; i < 5; ++i) {
+    Block k;
+    CHECK(block_cache().take((i + 1) * 1000 * MB, nullptr, k) == hipSuccess);
+    block_cache().give(k, nullptr);
+  }
+  size_t kept = 0;
+  for (auto &m : fake().live) kept += m.second;
+  CHECK(kept <= all / 8 && kept > 0);
+  block_cache().release();
+  CHECK(fake().live.empty() && fake().free == all && fake().mode == hipStreamCaptureModeGlobal);
+}
+
 int main(int argc, char **argv) {
   const char *what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "destroy")) {
@@ -92,6 +149,8 @@ int main(int argc, char **argv) {
     destroy_elsewhere();
   } else if (!std::strcmp(what, "create")) {
     create();
+  } else if (!std::strcmp(what, "room")) {
+    room();
   } else {
     std::printf("no check named '%s'\n", what);
     return 2;
