@@ -6,7 +6,8 @@
 // median with single steps of 0.1 to 3 s between, and takes 12.9 to 13.0 ms with its blocks kept here.
 // Blocks of 16 MB and more are therefore kept here.  A block belongs to one user at a time; when it is
 // given back an event marks the work that still uses it, and its next user's stream waits for that
-// event, so blocks pass between streams and threads safely.  At most an eighth of the device's memory is
+// event, so blocks pass between streams and threads safely.  A block that another stream's work still
+// uses is passed over while the library may have more memory, so that independent streams overlap.  At most an eighth of the device's memory is
 // kept (least recently used freed first), and a block that 1024 later returns did not need is freed.
 // Everything kept, and what the pool holds, goes back when any allocation of the library runs out of
 // memory (with_room) and when the program asks for it (release): other allocators of the process, torch's
@@ -30,6 +31,7 @@ struct Block {
   size_t bytes = 0;
   hipEvent_t evt = nullptr;  // (null: never kept) recorded at the last return, unless the device was idle then
   bool pending = false;      // evt may still have to be waited for
+  hipStream_t stream = nullptr;  // where evt was recorded
   int dev = -1;
   uint64_t stamp = 0;
 };
@@ -41,31 +43,27 @@ class BlockCache {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    {
-      std::lock_guard<std::mutex> lk(mu_);
-      size_t best = free_.size();
-      for (size_t i = 0; i < free_.size(); ++i) {
-        const Block &b = free_[i];
-        if (b.dev == dev && b.bytes >= bytes && b.bytes - bytes <= std::max(bytes / 2, kGrain) &&
-            (best == free_.size() || b.bytes < free_[best].bytes))
-          best = i;
-      }
-      if (best < free_.size()) {
-        out = free_[best];
-        free_.erase(free_.begin() + best);
-      }
+    bool more = false;  // another block is within the limit
+    if (find(dev, bytes, s, false, out, &more) || (!more && find(dev, bytes, s, true, out))) return use(out, s);
+    const Relaxed relaxed;
+    Block b;
+    b.bytes = (bytes + kGrain - 1) / kGrain * kGrain;
+    b.dev = dev;
+    e = hipMalloc(&b.p, b.bytes);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      if (find(dev, bytes, s, true, out)) return use(out, s);
+      release();
+      e = hipMalloc(&b.p, b.bytes);
     }
-    if (out.p) {
-      e = out.pending ? hipStreamWaitEvent(s, out.evt, 0) : hipSuccess;
-      if (e != hipSuccess) drop(out);
+    if (e != hipSuccess) return e;
+    e = hipEventCreateWithFlags(&b.evt, hipEventDisableTiming);
+    if (e != hipSuccess) {
+      (void)hipFree(b.p);
       return e;
     }
-    const Relaxed relaxed;
-    out.bytes = (bytes + kGrain - 1) / kGrain * kGrain;
-    out.dev = dev;
-    e = with_room([&] { return hipMalloc(&out.p, out.bytes); });
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&out.evt, hipEventDisableTiming);
-    if (e != hipSuccess) drop(out);
+    count(dev, b.bytes, true);
+    out = b;
     return e;
   }
 
@@ -115,6 +113,7 @@ class BlockCache {
       return;
     }
     b.pending = true;
+    b.stream = s;
     keep(b);
   }
 
@@ -154,12 +153,48 @@ class BlockCache {
     Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
     ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
   };
-  static void drop(Block &b) {
+  void drop(Block &b) {
     const Relaxed relaxed;
+    if (b.p && b.evt) count(b.dev, b.bytes, false);
     if (b.evt) (void)hipEventDestroy(b.evt);
     if (b.p) (void)hipFree(b.p);  // waits for the work that uses it
     (void)hipGetLastError();
     b = Block();
+  }
+  // a kept block in stream order on s
+  hipError_t use(Block &b, hipStream_t s) {
+    const hipError_t e = b.pending ? hipStreamWaitEvent(s, b.evt, 0) : hipSuccess;
+    if (e != hipSuccess) drop(b);
+    return e;
+  }
+  // the smallest kept block that fits: one whose work has ended or was on s, or (any) one to wait for;
+  // *more: whether a block of `bytes` on top of all that exist stays within the limit
+  bool find(int dev, size_t bytes, hipStream_t s, bool any, Block &out, bool *more = nullptr) {
+    const size_t most = limit(dev);
+    const Relaxed relaxed;
+    std::lock_guard<std::mutex> lk(mu_);
+    size_t best = free_.size();
+    for (size_t i = 0; i < free_.size(); ++i) {
+      Block &b = free_[i];
+      if (b.dev != dev || b.bytes < bytes || b.bytes - bytes > std::max(bytes / 2, kGrain)) continue;
+      if (!any && b.pending && b.stream != s) {
+        if (hipEventQuery(b.evt) != hipSuccess) {
+          (void)hipGetLastError();
+          continue;
+        }
+        b.pending = false;
+      }
+      if (best == free_.size() || b.bytes < free_[best].bytes) best = i;
+    }
+    if (more) *more = dev >= 0 && dev < 64 && owned_[dev] + bytes <= most;
+    if (best == free_.size()) return false;
+    out = free_[best];
+    free_.erase(free_.begin() + best);
+    return true;
+  }
+  void count(int dev, size_t bytes, bool up) {
+    std::lock_guard<std::mutex> lk(mu_);
+    if (dev >= 0 && dev < 64) owned_[dev] = up ? owned_[dev] + bytes : owned_[dev] - bytes;
   }
   size_t limit(int dev) {
     if (dev < 0 || dev >= 64) return 0;
@@ -190,6 +225,7 @@ class BlockCache {
   std::mutex mu_;
   std::vector<Block> free_;
   uint64_t clock_ = 0;
+  size_t owned_[64] = {};  // bytes of a device's blocks, kept and in use
   std::once_flag once_[64];
   size_t total_[64] = {};
 };

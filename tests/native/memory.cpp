@@ -142,6 +142,49 @@ static void room() {
   CHECK(fake().live.empty() && fake().free == all && fake().mode == hipStreamCaptureModeGlobal);
 }
 
+// independent streams whose calls overlap use different blocks, within the limit
+static void streams() {
+  ihipStream s1, s2;
+  fake().streams.insert(&s1);
+  fake().streams.insert(&s2);
+  auto call = [](hipStream_t s, size_t bytes) {  // take, enqueue, give back at once: as a library call does
+    Block b;
+    CHECK(block_cache().take(bytes, s, b) == hipSuccess);
+    void *const p = b.p;
+    ++s->issued;
+    block_cache().give(b, s);
+    return p;
+  };
+  auto ended = [](hipStream_t s) { s->ended = s->issued; };
+  const int waits = fake().waits;
+  void *const p1 = call(&s1, 64 * MB), *const p2 = call(&s2, 64 * MB);
+  CHECK(p1 != p2 && fake().waits == waits);
+  for (int i = 0; i < 8; ++i) CHECK(call(&s1, 64 * MB) == p1 && call(&s2, 64 * MB) == p2);
+  CHECK(fake().live.size() == 2);
+  // a third stream waits for nobody; once the first has ended its block is taken
+  ihipStream s3;
+  fake().streams.insert(&s3);
+  ended(&s1);
+  const int w = fake().waits;
+  CHECK(call(&s3, 64 * MB) == p1 && fake().waits == w && fake().live.size() == 2);
+  // above the limit (8 GB here) the pending block is waited for, and below it when there is no memory
+  ended(&s1), ended(&s2), ended(&s3);
+  block_cache().release();
+  void *const q1 = call(&s1, 7000 * MB);
+  CHECK(call(&s2, 7000 * MB) == q1 && fake().waits > w && fake().live.size() == 1);
+  ended(&s1), ended(&s2);
+  block_cache().release();
+  void *const r1 = call(&s1, 1000 * MB);
+  void *rest = nullptr;
+  CHECK(hipMalloc(&rest, fake().free) == hipSuccess);
+  CHECK(call(&s2, 1000 * MB) == r1);
+  (void)hipFree(rest);
+  ended(&s1), ended(&s2);
+  block_cache().release();
+  CHECK(fake().live.empty());
+  for (ihipStream *s : {&s1, &s2, &s3}) fake().streams.erase(s);
+}
+
 int main(int argc, char **argv) {
   const char *what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "destroy")) {
@@ -151,6 +194,8 @@ int main(int argc, char **argv) {
     create();
   } else if (!std::strcmp(what, "room")) {
     room();
+  } else if (!std::strcmp(what, "streams")) {
+    streams();
   } else {
     std::printf("no check named '%s'\n", what);
     return 2;
