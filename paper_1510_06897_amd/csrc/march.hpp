@@ -217,7 +217,8 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
   const MarchPlace mp = march_place(I, ex, gb - I.mblk0);
   const int r = mp.r, t0 = mp.t0, t1 = mp.t1, n = mp.n, V3 = ex.st;
   const int tid = threadIdx.x;
-  const bool active = mp.tile_lane(tid), hactive = mp.face_lane(tid);
+  // (a tile is whole waves: one answer per wave, and scalar branches on it)
+  const bool active = __builtin_amdgcn_readfirstlane(mp.tile_lane(tid)) != 0, hactive = mp.face_lane(tid);
   const int sj = active ? tid : 0;
   const MarchSite ms = march_site(mp, I, ex, sj);
   const int jxp = ms.jxp, jxm = ms.jxm, jyp = ms.jyp, jym = ms.jym, jzp = ms.jzp, jzm = ms.jzm;
@@ -284,7 +285,16 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
     link(lo, 1, t, k2);
     link(ly, 1, t, k3);
   };
-  if (active) {
+  if (!active) {  // a wave beside the tile: its share of the faces, and the barriers of the others
+    for (int t = t0; t < t1; ++t) {
+      if (hactive) load12(vh, t, hu, hd);
+      if (t > t0) __syncthreads();
+      if (hactive) put12(n + tid, hu, hd);
+      __syncthreads();
+    }
+    return;
+  }
+  {
     const int tm = t0 == 0 ? ex.lt - 1 : t0 - 1;
     cx<C> h[2][3];
     load12(vo, t0, pu, pd);
@@ -297,9 +307,6 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
     half_project<3, -1>(pu, pd, s5, h);
     half_mul<true>(k0, h, bt);
     links4(t0);
-  } else if (hactive) {  // a wave with faces only
-    load12(vh, t0, hu, hd);
-    put12(n + tid, hu, hd);
   }
   __syncthreads();
   using I0 = std::integral_constant<int, 0>;
@@ -310,96 +317,90 @@ __global__ void __launch_bounds__(kMarchThreads, sizeof(C) == 4 ? 2 : 1)
   // before it: x and y links (issued before the barrier), the z links, the t + 1 slice, the t link,
   // psi and w.
   for (int t = t0; t < t1; ++t) {
-    if (active) {
-      const uint32_t so = (uint32_t)t * ts;
-      cx<C> acc[12], dir[12], wv[12], sv[12];  // hopping sum, one direction's part, w and psi
-      auto settle = [&](cx<C> *q) {
+    const uint32_t so = (uint32_t)t * ts;
+    cx<C> acc[12], dir[12], wv[12], sv[12];  // hopping sum, one direction's part, w and psi
+    auto settle = [&](cx<C> *q) {
 #pragma unroll
-        for (int i = 0; i < 12; ++i) pin(q[i]);
-        __builtin_amdgcn_sched_barrier(0);
-      };
-      auto hop = [&](auto mu_, auto sg_, int j, cx<C> m[3][3]) {
-        constexpr int MU = decltype(mu_)::value, SG = decltype(sg_)::value;
-        cx<C> u[2][3], d[2][3], h[2][3], rr[2][3];
-        if (SG > 0) {
-#pragma unroll
-          for (int i = 0; i < 12; ++i) dir[i] = mk<C>(0, 0);
-        }
-        get12(j, u, d);
-        half_project<MU, SG>(u, d, s5, h);
-        if (R12) su3_row2(m);
-        half_mul<(SG < 0)>(m, h, rr);
-        half_add<MU, SG>(dir, rr);
-        settle(dir);
-      };
-      // the directions' parts are added in the order of the direction-split kernels, ((x + y) + z) + t
-      // with forward before backward, so that every launch form gives the same bits
-      auto add_dir = [&]() {
-#pragma unroll
-        for (int i = 0; i < 12; ++i) acc[i] = acc[i] + dir[i];
-      };
-      hop(I0{}, I1{}, jxp, k0);
-      hop(I0{}, M1{}, jxm, k1);
-#pragma unroll
-      for (int i = 0; i < 12; ++i) acc[i] = dir[i];
-      settle(acc);
-      link(lo, 2, t, k0);
-      link(lz, 2, t, k1);
+      for (int i = 0; i < 12; ++i) pin(q[i]);
       __builtin_amdgcn_sched_barrier(0);
-      hop(I1{}, I1{}, jyp, k2);
-      hop(I1{}, M1{}, jym, k3);
-      add_dir();
-      settle(acc);
-      const int tn = t + 1 == ex.lt ? 0 : t + 1;
-      load12(vo, tn, pu, pd);
-      if (hactive && t + 1 < t1) load12(vh, tn, hu, hd);
-      __builtin_amdgcn_sched_barrier(0);
-      hop(I2{}, I1{}, jzp, k0);
-      hop(I2{}, M1{}, jzm, k1);
-      add_dir();
-      settle(acc);
-      link(lo, 3, t, k2);
-#pragma unroll
-      for (int i = 0; i < 12; ++i) sv[i] = bio<SE, C>::ld(sr, vo, so + i * cs);
-#pragma unroll
-      for (int i = 0; i < 12; ++i) wv[i] = bio<SE, C>::ld(w, vo, so + i * cs);
-      __builtin_amdgcn_sched_barrier(0);
-      // t forward with the t + 1 slice, t backward with the carried half-spinor, and the one carried on
+    };
+    auto hop = [&](auto mu_, auto sg_, int j, cx<C> m[3][3]) {
+      constexpr int MU = decltype(mu_)::value, SG = decltype(sg_)::value;
       cx<C> u[2][3], d[2][3], h[2][3], rr[2][3];
+      if (SG > 0) {
 #pragma unroll
-      for (int i = 0; i < 12; ++i) dir[i] = mk<C>(0, 0);
-      half_project<3, 1>(pu, pd, s5, h);
-      if (R12) su3_row2(k2);
-      half_mul<false>(k2, h, rr);
-      half_add<3, 1>(dir, rr);
-      half_add<3, -1>(dir, bt);
-      add_dir();
-      settle(acc);
-      get12(sj, u, d);
-      half_project<3, -1>(u, d, s5, h);
-      half_mul<true>(k2, h, bt);
-#pragma unroll
-      for (int i = 0; i < 12; ++i) {
-        const cx<C> v0 = i < 6 ? u[i / 3][i % 3] : d[i / 3 - 2][i % 3];
-        const cx<C> xv = i < 6 ? v0 : mk<C>(s5 * v0.re, s5 * v0.im);
-        // the roundings of the direction-split kernels, spelled out
-        cx<C> yv = mk<C>(fma(kd, xv.re, kh * acc[i].re), fma(kd, xv.im, kh * acc[i].im));
-        if (i >= 6) yv = mk<C>(sy * yv.re, sy * yv.im);
-        const C ai = i < 6 ? al : ah;
-        yv = mk<C>(fma(ai, sv[i].re, yv.re), fma(ai, sv[i].im, yv.im));
-        acc[i] = mk<C>(fma(tw, wv[i].re, yv.re), fma(tw, wv[i].im, yv.im));
+        for (int i = 0; i < 12; ++i) dir[i] = mk<C>(0, 0);
       }
+      get12(j, u, d);
+      half_project<MU, SG>(u, d, s5, h);
+      if (R12) su3_row2(m);
+      half_mul<(SG < 0)>(m, h, rr);
+      half_add<MU, SG>(dir, rr);
+      settle(dir);
+    };
+    // the directions' parts are added in the order of the direction-split kernels, ((x + y) + z) + t
+    // with forward before backward, so that every launch form gives the same bits
+    auto add_dir = [&]() {
 #pragma unroll
-      for (int i = 0; i < 12; ++i) bio<SE, C>::st(o, vo, so + i * cs, acc[i]);
-    } else if (hactive && t + 1 < t1) {
-      load12(vh, t + 1, hu, hd);
+      for (int i = 0; i < 12; ++i) acc[i] = acc[i] + dir[i];
+    };
+    hop(I0{}, I1{}, jxp, k0);
+    hop(I0{}, M1{}, jxm, k1);
+#pragma unroll
+    for (int i = 0; i < 12; ++i) acc[i] = dir[i];
+    settle(acc);
+    link(lo, 2, t, k0);
+    link(lz, 2, t, k1);
+    __builtin_amdgcn_sched_barrier(0);
+    hop(I1{}, I1{}, jyp, k2);
+    hop(I1{}, M1{}, jym, k3);
+    add_dir();
+    settle(acc);
+    const int tn = t + 1 == ex.lt ? 0 : t + 1;
+    load12(vo, tn, pu, pd);
+    if (hactive && t + 1 < t1) load12(vh, tn, hu, hd);
+    __builtin_amdgcn_sched_barrier(0);
+    hop(I2{}, I1{}, jzp, k0);
+    hop(I2{}, M1{}, jzm, k1);
+    add_dir();
+    settle(acc);
+    link(lo, 3, t, k2);
+#pragma unroll
+    for (int i = 0; i < 12; ++i) sv[i] = bio<SE, C>::ld(sr, vo, so + i * cs);
+#pragma unroll
+    for (int i = 0; i < 12; ++i) wv[i] = bio<SE, C>::ld(w, vo, so + i * cs);
+    __builtin_amdgcn_sched_barrier(0);
+    // t forward with the t + 1 slice, t backward with the carried half-spinor, and the one carried on
+    cx<C> u[2][3], d[2][3], h[2][3], rr[2][3];
+#pragma unroll
+    for (int i = 0; i < 12; ++i) dir[i] = mk<C>(0, 0);
+    half_project<3, 1>(pu, pd, s5, h);
+    if (R12) su3_row2(k2);
+    half_mul<false>(k2, h, rr);
+    half_add<3, 1>(dir, rr);
+    half_add<3, -1>(dir, bt);
+    add_dir();
+    settle(acc);
+    get12(sj, u, d);
+    half_project<3, -1>(u, d, s5, h);
+    half_mul<true>(k2, h, bt);
+#pragma unroll
+    for (int i = 0; i < 12; ++i) {
+      const cx<C> v0 = i < 6 ? u[i / 3][i % 3] : d[i / 3 - 2][i % 3];
+      const cx<C> xv = i < 6 ? v0 : mk<C>(s5 * v0.re, s5 * v0.im);
+      // the roundings of the direction-split kernels, spelled out
+      cx<C> yv = mk<C>(fma(kd, xv.re, kh * acc[i].re), fma(kd, xv.im, kh * acc[i].im));
+      if (i >= 6) yv = mk<C>(sy * yv.re, sy * yv.im);
+      const C ai = i < 6 ? al : ah;
+      yv = mk<C>(fma(ai, sv[i].re, yv.re), fma(ai, sv[i].im, yv.im));
+      acc[i] = mk<C>(fma(tw, wv[i].re, yv.re), fma(tw, wv[i].im, yv.im));
     }
+#pragma unroll
+    for (int i = 0; i < 12; ++i) bio<SE, C>::st(o, vo, so + i * cs, acc[i]);
     if (t + 1 < t1) {
       __syncthreads();
-      if (active) {
-        links4(t + 1);
-        put12(sj, pu, pd);
-      }
+      links4(t + 1);
+      put12(sj, pu, pd);
       if (hactive) put12(n + tid, hu, hd);
       __syncthreads();
     }
