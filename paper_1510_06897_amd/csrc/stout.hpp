@@ -14,110 +14,12 @@
 // through raw buffer resources (lane offset site * 16 bytes, element offset in a scalar register),
 // so a field must span less than 4 GiB.  A thread owns one link
 // (site, mu); the workgroup's 256 threads share mu, so the path loops below are uniform over a
-// wave.  exp(M) is a Taylor series on the Cayley-Hamilton coefficients after scaling M to norm
-// <= 1/2, followed by squaring; the Frechet derivative of exp comes from the same series.
+// wave.  exp(M) and its Frechet derivative: m3.hpp.
 #pragma once
 
-#include "common.hpp"
+#include "m3.hpp"
 
 namespace ovl {
-
-// ---------------------------------------------------------------------------------------------
-// 3 x 3 complex FP64 matrices in registers
-struct M3 {
-  cx<double> e[3][3];
-};
-
-__device__ __forceinline__ M3 m3_zero() {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) r.e[i][j] = mk<double>(0.0, 0.0);
-  return r;
-}
-__device__ __forceinline__ M3 m3_unit() {
-  M3 r = m3_zero();
-#pragma unroll
-  for (int i = 0; i < 3; ++i) r.e[i][i] = mk<double>(1.0, 0.0);
-  return r;
-}
-// A B
-__device__ __forceinline__ M3 m3_mul(const M3 &a, const M3 &b) {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      cx<double> s = mk<double>(0.0, 0.0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) s = cmadd(s, a.e[i][k], b.e[k][j]);
-      r.e[i][j] = s;
-    }
-  return r;
-}
-// A^+ B
-__device__ __forceinline__ M3 m3_dmul(const M3 &a, const M3 &b) {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      cx<double> s = mk<double>(0.0, 0.0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) s = cjmadd(s, a.e[k][i], b.e[k][j]);
-      r.e[i][j] = s;
-    }
-  return r;
-}
-// A B^+
-__device__ __forceinline__ M3 m3_muld(const M3 &a, const M3 &b) {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      cx<double> s = mk<double>(0.0, 0.0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) s = cjmadd(s, b.e[j][k], a.e[i][k]);
-      r.e[i][j] = s;
-    }
-  return r;
-}
-__device__ __forceinline__ M3 m3_dag(const M3 &a) {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) r.e[i][j] = mk<double>(a.e[j][i].re, -a.e[j][i].im);
-  return r;
-}
-// a + s b
-__device__ __forceinline__ M3 m3_axpy(const M3 &a, double s, const M3 &b) {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      r.e[i][j] = mk<double>(fma(s, b.e[i][j].re, a.e[i][j].re), fma(s, b.e[i][j].im, a.e[i][j].im));
-  return r;
-}
-__device__ __forceinline__ M3 m3_scale(const M3 &a, double s) {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) r.e[i][j] = scale(a.e[i][j], s);
-  return r;
-}
-__device__ __forceinline__ double m3_frob(const M3 &a) {
-  double s = 0.0;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) s += a.e[i][j].re * a.e[i][j].re + a.e[i][j].im * a.e[i][j].im;
-  return sqrt(s);
-}
 
 // element (a, b) of link `dir` at `site`: U[dir][a][b][site]
 __device__ __forceinline__ M3 load_m3(const double2 *__restrict__ U, int dir, int site, int V) {
@@ -139,154 +41,6 @@ __device__ __forceinline__ void store_m3(double2 *__restrict__ U, int dir, int s
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j) p[(int64_t)(3 * i + j) * V] = make_double2(m.e[i][j].re, m.e[i][j].im);
-}
-
-// ---------------------------------------------------------------------------------------------
-// exp(A) and the Frechet derivative L(A, F) = d/dt exp(A + t F) at t = 0 for traceless A.
-//   Scale: X = A / 2^s with ||X||_F <= 1/2.  Series: a traceless 3 x 3 matrix obeys (Cayley-Hamilton)
-//   X^3 = p X + q, p = tr(X^2) / 2, q = det X, so every term X^k / k! is a_k + b_k X + c_k X^2 with
-//   a' = c q / (k + 1), b' = (a + c p) / (k + 1), c' = b / (k + 1): the series runs on three complex
-//   numbers and exp(X) = f0 + f1 X + f2 X^2 takes one matrix product.  The derivative along a traceless
-//   G changes p by tr(X G) and q by tr(X^2 G):
-//     L(X, G) = f1 G + f2 (X G + G X) + df0 + df1 X + df2 X^2,  df = f_p tr(X G) + f_q tr(X^2 G),
-//   with the p and q derivatives of a, b, c carried along; a trace of F adds (tr F / 3) exp(X).
-//   Square: exp(2Y) = exp(Y)^2 and L(2Y, 2G) = L(Y, G) exp(Y) + exp(Y) L(Y, G).
-// 18 terms leave a remainder below 0.5^19 / 19! (1e-23) of the scaled series.  (The same series as
-// matrix powers took 18 products for exp and 54 for the derivative.)
-constexpr int kExpTerms = 18;
-
-__device__ __forceinline__ int exp_scaling(const M3 &a) {
-  double n = m3_frob(a);
-  int s = 0;
-  while (n > 0.5 && s < 40) {
-    n *= 0.5;
-    ++s;
-  }
-  return s;
-}
-
-using cxd = cx<double>;
-__device__ __forceinline__ cxd cmul(cxd a, cxd b) { return cmadd(mk<double>(0.0, 0.0), a, b); }
-// tr(A B)
-__device__ __forceinline__ cxd m3_trmul(const M3 &a, const M3 &b) {
-  cxd t = mk<double>(0.0, 0.0);
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) t = cmadd(t, a.e[i][k], b.e[k][i]);
-  return t;
-}
-__device__ __forceinline__ cxd m3_det(const M3 &a) {
-  cxd d = mk<double>(0.0, 0.0);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const int j = (i + 1) % 3, k = (i + 2) % 3;
-    const cxd m = cmadd(cmul(a.e[1][j], a.e[2][k]), -a.e[1][k], a.e[2][j]);
-    d = cmadd(d, a.e[0][i], m);
-  }
-  return d;
-}
-// r += s A, s complex
-__device__ __forceinline__ void m3_cacc(M3 &r, cxd s, const M3 &a) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) r.e[i][j] = cmadd(r.e[i][j], s, a.e[i][j]);
-}
-__device__ __forceinline__ M3 m3_cdiag(cxd s) {
-  M3 r = m3_zero();
-#pragma unroll
-  for (int i = 0; i < 3; ++i) r.e[i][i] = s;
-  return r;
-}
-
-__device__ inline M3 m3_exp(const M3 &m) {
-  const int s = exp_scaling(m);
-  const M3 x = m3_scale(m, ldexp(1.0, -s));
-  const M3 x2 = m3_mul(x, x);
-  const cxd p = scale(x2.e[0][0] + x2.e[1][1] + x2.e[2][2], 0.5), q = m3_det(x);
-  cxd a = mk<double>(1.0, 0.0), b = mk<double>(0.0, 0.0), c = b;
-  cxd f0 = a, f1 = b, f2 = b;
-  for (int k = 1; k <= kExpTerms; ++k) {
-    const double r = 1.0 / k;
-    const cxd an = scale(cmul(c, q), r), bn = scale(cmadd(a, c, p), r), cn = scale(b, r);
-    a = an;
-    b = bn;
-    c = cn;
-    f0 = f0 + a;
-    f1 = f1 + b;
-    f2 = f2 + c;
-  }
-  M3 e = m3_cdiag(f0);
-  m3_cacc(e, f1, x);
-  m3_cacc(e, f2, x2);
-  for (int i = 0; i < s; ++i) e = m3_mul(e, e);
-  return e;
-}
-
-// exp(A) into *e and L(A, F) into *l
-__device__ inline void m3_exp_frechet(const M3 &m, const M3 &f, M3 *e_out, M3 *l_out) {
-  const int s = exp_scaling(m);
-  const double sc = ldexp(1.0, -s);
-  const M3 x = m3_scale(m, sc);
-  M3 g = m3_scale(f, sc);
-  const cxd tr = scale(g.e[0][0] + g.e[1][1] + g.e[2][2], 1.0 / 3.0);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) g.e[i][i] = g.e[i][i] - tr;
-  const M3 x2 = m3_mul(x, x);
-  const cxd p = scale(x2.e[0][0] + x2.e[1][1] + x2.e[2][2], 0.5), q = m3_det(x);
-  const cxd dp = m3_trmul(x, g), dq = m3_trmul(x2, g);
-  const cxd zero = mk<double>(0.0, 0.0);
-  cxd a = mk<double>(1.0, 0.0), b = zero, c = zero;
-  cxd ad = zero, bd = zero, cd = zero;  // derivatives of a, b, c along (dp, dq)
-  cxd f0 = a, f1 = zero, f2 = zero, g0 = zero, g1 = zero, g2 = zero;
-  for (int k = 1; k <= kExpTerms; ++k) {
-    const double r = 1.0 / k;
-    const cxd an = scale(cmul(c, q), r), bn = scale(cmadd(a, c, p), r), cn = scale(b, r);
-    const cxd adn = scale(cmadd(cmul(cd, q), c, dq), r);
-    const cxd bdn = scale(cmadd(cmadd(ad, cd, p), c, dp), r), cdn = scale(bd, r);
-    a = an;
-    b = bn;
-    c = cn;
-    ad = adn;
-    bd = bdn;
-    cd = cdn;
-    f0 = f0 + a;
-    f1 = f1 + b;
-    f2 = f2 + c;
-    g0 = g0 + ad;
-    g1 = g1 + bd;
-    g2 = g2 + cd;
-  }
-  M3 e = m3_cdiag(f0);
-  m3_cacc(e, f1, x);
-  m3_cacc(e, f2, x2);
-  M3 l = m3_cdiag(g0);
-  m3_cacc(l, f1, g);
-  m3_cacc(l, g1, x);
-  m3_cacc(l, g2, x2);
-  m3_cacc(l, f2, m3_axpy(m3_mul(x, g), 1.0, m3_mul(g, x)));
-  m3_cacc(l, tr, e);
-  for (int i = 0; i < s; ++i) {
-    l = m3_axpy(m3_mul(l, e), 1.0, m3_mul(e, l));
-    e = m3_mul(e, e);
-  }
-  *e_out = e;
-  *l_out = l;
-}
-
-// traceless anti-Hermitian part: (W - W^+)/2 - tr(W - W^+)/6
-__device__ __forceinline__ M3 m3_ta(const M3 &w) {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      r.e[i][j] = mk<double>(0.5 * (w.e[i][j].re - w.e[j][i].re), 0.5 * (w.e[i][j].im + w.e[j][i].im));
-  const double tr_im = (r.e[0][0].im + r.e[1][1].im + r.e[2][2].im) / 3.0;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) r.e[i][i].im -= tr_im;
-  return r;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -479,7 +233,7 @@ __global__ void __launch_bounds__(256)
   const int mu = blockIdx.y;
   if (site >= V) return;
   const M3 c = load_m3(C, mu, site, V), u = load_m3(U, mu, site, V);
-  store_m3(out, mu, site, V, m3_mul(m3_exp(m3_ta(m3_muld(c, u))), u));
+  store_m3(out, mu, site, V, m3_axpy(u, 1.0, m3_mul(m3_expm1(m3_ta(m3_muld(c, u))), u)));
 }
 
 // Backward of one step, the part local to each link.  With G' = dL/dRe U' + i dL/dIm U' of the
@@ -500,11 +254,11 @@ __global__ void __launch_bounds__(256)
   const M3 m = m3_ta(m3_muld(c, u));
   const M3 gp = load_m3(gout, mu, site, V);
   // exp(M^+) = exp(-M) = E^+ (M is anti-Hermitian), and dL/dM = L(M^+, G' U^+)
-  M3 ed, gm;
-  m3_exp_frechet(m3_scale(m, -1.0), m3_muld(gp, u), &ed, &gm);
+  M3 ed, gm;  // E^+ - 1
+  m3_expm1_frechet(m3_scale(m, -1.0), m3_muld(gp, u), &ed, &gm);
   const M3 go = m3_ta(gm);
   store_m3(gamma, mu, site, V, m3_mul(go, u));
-  store_m3(direct, mu, site, V, m3_axpy(m3_mul(ed, gp), 1.0, m3_dmul(go, c)));
+  store_m3(direct, mu, site, V, m3_axpy(gp, 1.0, m3_muladd(m3_dmul(go, c), ed, gp)));
 }
 
 // Backward of one step, the staple part.  Link (y, d) receives w A^+ Gamma_nu(x) B^+ (its adjoint

@@ -13,7 +13,7 @@ def run(name, tmp_path, *args):
     prog, src = str(tmp_path / os.path.splitext(name)[0]), os.path.join(NATIVE, name)
     if name.endswith(".hip"):
         flags = [f for f in build.FLAGS if f not in ("-fPIC", "-shared", "-O3")]
-        cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "-O1"]
+        cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "-O1", "-Xarch_host", "-mfma"]
     else:
         cmd = ["g++", "-std=c++17", "-O1", "-g", "-Wall", "-pthread", "-I" + os.path.join(NATIVE, "stub")]
     made = subprocess.run([*cmd, "-o", prog, src], capture_output=True, text=True)
