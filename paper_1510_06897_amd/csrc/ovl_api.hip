@@ -487,18 +487,26 @@ int64_t items_work(const StepItem *items, int n) {
   return w;
 }
 
+// Lets a kernel use `bytes` of dynamic LDS on the current device; `done` (one per kernel) remembers the
+// devices where it may.
+int allow_lds(const void *kernel, int bytes, std::atomic<uint64_t> &done) {
+  int dev = 0;
+  HIP_TRY(hipGetDevice(&dev));
+  const uint64_t bit = dev >= 0 && dev < 64 ? uint64_t(1) << dev : 0;
+  if (done.load(std::memory_order_relaxed) & bit) return OVL_OK;
+  HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+  done.fetch_or(bit, std::memory_order_relaxed);
+  return OVL_OK;
+}
+
 // launch one step; a single-problem launch plans its item here, a table launch was planned when
 // its table was written (p.total_blocks, spb)
 template <class C, class SE, class LE, int NW, bool R12>
 int launch_slab(StepArgs<false> &p, hipStream_t s) {
   const int bytes = slab_lds_bytes<C>(64 * NW, p.item.g.L[0]);
-  static std::once_flag once;
-  static hipError_t attr = hipSuccess;
-  std::call_once(once, [] {
-    attr = hipFuncSetAttribute((const void *)step_slab_kernel<C, SE, LE, NW, false, R12>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 512);
-  });
-  HIP_TRY(attr);
+  static std::atomic<uint64_t> done{0};
+  const int rc = allow_lds((const void *)step_slab_kernel<C, SE, LE, NW, false, R12>, 160 * 1024 - 512, done);
+  if (rc) return rc;
   step_slab_kernel<C, SE, LE, NW, false, R12><<<p.total_blocks, 256 * NW, bytes, s>>>(p);
   HIP_TRY(hipGetLastError());
   return OVL_OK;
@@ -602,13 +610,9 @@ int launch_step_r(StepArgs<TABLE> &p, const LaunchCfg &cfg, hipStream_t s) {
 template <class C, class SE, class LE, bool TABLE, bool R12>
 int launch_march(StepArgs<TABLE> &p, hipStream_t s) {
   constexpr int bytes = march_lds_bytes<C>();
-  static std::once_flag once;
-  static hipError_t attr = hipSuccess;
-  std::call_once(once, [] {
-    attr = hipFuncSetAttribute((const void *)march_kernel<C, SE, LE, TABLE, R12>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  });
-  HIP_TRY(attr);
+  static std::atomic<uint64_t> done{0};
+  const int rc = allow_lds((const void *)march_kernel<C, SE, LE, TABLE, R12>, bytes, done);
+  if (rc) return rc;
   march_kernel<C, SE, LE, TABLE, R12><<<p.march_blocks, kMarchThreads, bytes, s>>>(p);
   HIP_TRY(hipGetLastError());
   return OVL_OK;
