@@ -27,8 +27,9 @@
  *           weights and the final norm check.
  * Pointers: "_dev" pointers are device memory of the current HIP device, "_host" pointers host
  *           memory.  The caller owns every data pointer; the library owns only its handles, the
- *           temporaries it allocates (stream-ordered, freed before the call's work ends) and the
- *           work vectors of its cached step graphs (see ovl_graph_enable).
+ *           temporaries it allocates (stream-ordered, free for other calls when the call's work ends;
+ *           large ones are kept between calls, see ovl_memory_release) and the work vectors of its
+ *           cached step graphs (see ovl_graph_enable).
  * Streams:  every operator is enqueued on the caller's stream (a hipStream_t passed as void*,
  *           NULL for the null stream) and is asynchronous: results are visible after the stream
  *           synchronises.  Calls that share a handle may run on different streams only if they do
@@ -213,9 +214,9 @@ int ovl_wilson_link_vjp(const ovl_gauge *g, void *G_dev, const void *chi, const 
 /* G_dev = d Re <chi, p(X) psi> / dU with p the polynomial of the handle (no deflation term,
  * lmax held fixed): reverse Clenshaw sweep on chi with the forward Chebyshev vectors of psi
  * recomputed from checkpoints every ckpt_stride steps.  0: all N forward vectors are kept (N + 66
- * vectors of work space, from the device's memory pool, which retains it for later calls) where that is
- * at most a tenth of the device's memory and can be allocated, else checkpoints every ceil(sqrt(N))
- * steps; under stream capture always checkpoints.  The recomputation
+ * vectors of work space) where that is at most a tenth of the device's memory and can be allocated,
+ * else checkpoints every ceil(sqrt(N)) steps; under stream capture always checkpoints.  Work space of
+ * 16 MB and more stays with the library for later calls (see ovl_memory_release).  The recomputation
  * and the reverse sweep of a segment are independent, so their steps run two at a time in one
  * launch that reads the links once (the launch configuration of a two-right-hand-side problem on
  * this lattice, see ovl_autotune).  Layout of G_dev as in ovl_wilson_link_vjp; single right-hand
@@ -378,8 +379,8 @@ int ovl_overlap_solve_gmresr(const ovl_gauge *g, const ovl_poly *p, const ovl_de
  * (eight threads per site: forward and backward hops on separate threads), 16 or 64 (four threads
  * per site) or 128 (two x-adjacent sites per lane).  Order 2 = LDS slab of whole x lines with
  * spb = 64, 128, 192 or 256 sites (single problems; spb a multiple of Lx dividing Lx Ly).  Order 3 =
- * plain steps in the t-marching form (tiles of whole x lines marched through t, up to 256 sites a
- * tile; the final step as order 1), spb = 64, rb = 1.
+ * plain steps in the t-marching form (tiles of whole x lines marched through t, up to 256 sites and
+ * 256 face sites a tile; the final step as order 1), spb = 64, rb = 1.
  * Remap = XCD-contiguous workgroup ranges on or off.  rb = right-hand-side block: 1, 2 or 4
  * right-hand sides per thread reusing one read of the thread's two links (spb 16 or 64, orders
  * 0 and 1).  Each candidate runs 2 untimed and 10 timed steps that read the items' inputs and
@@ -401,8 +402,10 @@ int ovl_autotune_load(const char *cache_path);
 /* The configuration the library will use for a single problem: cfg_out = {sites per workgroup,
  * order, remap} (see ovl_autotune).  Defaults: 8 sites per workgroup below 4K
  * site-right-hand-sides, 16 below 64K, else 64 in tile order, with 128 (two sites per lane) for
- * FP32 links from 512K site-right-hand-sides; order 3 with 64 where a tile fits every lattice and a
- * step's vectors and links exceed 256 MB; remap on; rb 1.  Two sites per lane need FP32
+ * FP32 links from 512K site-right-hand-sides; with 16-bit links memory order (0) while a step's three
+ * vectors and the links are below 120 MB; order 3 with 64 where a tile fits every lattice, at least half
+ * of the sites (times right-hand sides) lie in 256-site tiles, and a step's vectors and links reach 256
+ * MB; remap on; rb 1.  Two sites per lane need FP32
  * spinors, an even Lx and 16-byte aligned vectors (a call whose vectors are not aligned runs
  * with 64); a slab or t-marching entry that does not fit the lattice falls back to the
  * default. */

@@ -952,8 +952,8 @@ __global__ void __launch_bounds__(kBlock)
 // data: v_mfma_f64_16x16x4f64, FP64 throughout.  The four waves of a workgroup are added in FP64 in
 // fixed order and pass 2 sums the workgroups in FP64.
 // Bound by memory: the bytes are the basis and the right-hand sides once each (24 FP64 vectors and 12
-// right-hand sides of 16^3 x 32: 906 MB in 228 us, 4.0 TB/s; the VALU kernel, which reads the basis
-// once per right-hand side, takes 1.35 ms).
+// right-hand sides of 16^3 x 32: 906 MB in 246 us with pass 2, 3.7 TB/s; the VALU kernel, which reads the
+// basis once per right-hand side, takes 1.35 ms).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaT = 4;  // reals per lane per step
@@ -1184,7 +1184,7 @@ __global__ void __launch_bounds__(kBlock)
 // A thread owns one spin-colour component of one site for up to RB right-hand sides: every basis
 // element read feeds RB multiply-adds, so the basis is read once per RB right-hand sides; the
 // coefficients w c of the launch sit in LDS.  Bound by memory (24 FP64 vectors added to 12 right-hand
-// sides of 16^3 x 32: 1.21 GB in 272 us, 4.4 TB/s; with the basis read once per right-hand side
+// sides of 16^3 x 32: 1.21 GB in 264 us, 4.6 TB/s; with the basis read once per right-hand side
 // 1445 us).  Every sum runs over i in ascending order.
 constexpr int kWChunk = 256;  // basis vectors per launch
 constexpr int kWStage = 64;   // of which this many have their coefficients in LDS at a time

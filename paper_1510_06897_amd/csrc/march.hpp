@@ -3,19 +3,20 @@
 //
 // A workgroup owns a tile of whole x lines, Lx x ty x tz (up to 256) sites of one (x, y, z)
 // cross-section, and marches it through a chunk of consecutive t.  The tile's input spinors of the
-// current t, with the faces y0 + ty, y0 - 1, z0 + tz, z0 - 1 (periodic), sit in LDS: the x, y and z
-// neighbours and the own value are read from there.  The t + 1 slice is read into registers during
+// current t, with the faces y0 + ty, y0 - 1, z0 + tz, z0 - 1 (periodic; up to 256 face sites, of which
+// there may be more than tile sites), sit in LDS: the x, y and z neighbours and the own value are read
+// from there.  The t + 1 slice is read into registers during
 // the step (the forward t neighbour of this slice, the LDS contents of the next), and the backward
 // t hop is carried as the half-spinor U_t^+ h(t), formed with the link the forward t hop reads.
 //
 // Why: the direction-split kernels read every spinor eight times and every link twice through L1 and
-// L2.  With vectors beyond the last-level cache the re-reads that miss L2 are what they wait for: one
-// launch on 64 FP64 vectors of 16^3 x 32 reads 9.7 GB from beyond L2, 6.8 GB here, and K plus the
-// fused K step on that block takes 2.77 ms instead of 3.66.  Bound by HBM: the 18 right-hand sides of
-// 12 x 16^3 x 32 + 4 x 8^3 x 16 + 2 x 12^3 x 24 in FP32 with two-row links move 733 MB in 167 us, 4.4
-// TB/s (a plain copy: 4.9), instead of 785 MB in 178 us; the degree-299 sign function 49.2 instead of
-// 55.5 ms.
-// The registers (FP32 about 225, FP64 about 400 of 512) leave two FP32 waves or one FP64 wave per
+// L2.  With vectors beyond the last-level cache the re-reads that miss L2 are what they wait for: K and
+// the fused K step on 64 FP64 vectors of 16^3 x 32 read 5.4 and 9.5 GB from beyond L2 (their bytes: 1.7
+// and 3.3), 4.3 and 7.5 GB here, and take 2.74 ms together instead of 3.65.  Bound by HBM: the 18 right-hand sides of
+// 12 x 16^3 x 32 + 4 x 8^3 x 16 + 2 x 12^3 x 24 in FP32 with two-row links move 861 MB in 163 us (5.3
+// TB/s; a plain copy: 4.9), the direction-split pair kernel 813 MB in 184 us: in this case the gain is
+// the rate, not fewer bytes; the degree-299 sign function takes 49.4 instead of 56.0 ms.
+// The registers (FP32 232 to 250, FP64 440 to 476 of 512) leave two FP32 waves or one FP64 wave per
 // SIMD, so the loads of a step are issued in a few groups well ahead of their use instead of relying
 // on other waves: with each hop waiting for its own link loads the FP64 launches took 1.3x longer.
 #pragma once

@@ -1,17 +1,18 @@
 // Device memory kept between calls: large work spaces and link fields.
 //
-// The device's stream-ordered pool gives its free memory back whenever something calls hipFree (every
-// gauge handle did when it was destroyed), and the next large allocation then maps memory anew: a loop of
-// handle, smearing, chain rule, force and sign function on 16^3 x 32 in FP64 took 19.8 ms a step in the
-// median with single steps of 0.1 to 3 s between, and takes 12.9 to 13.0 ms with its blocks kept here.
+// The device's stream-ordered pool does not keep them: whatever its release threshold, it gives free blocks
+// back at any hipFree and at most calls of hipFreeAsync (a free 4 GB block was gone when the next, of 64 MB,
+// was freed), and memory that was just given back is slow to map again (23 GB: 0.6 s).  A loop of handle,
+// smearing, chain rule, force and sign function on 16^3 x 32 in FP64 takes 12.9 ms a step, 13.2 at most,
+// with its blocks kept here; from the pool single steps took up to 1.4 s.
 // Blocks of 16 MB and more are therefore kept here.  A block belongs to one user at a time; when it is
 // given back an event marks the work that still uses it, and its next user's stream waits for that
 // event, so blocks pass between streams and threads safely.  A block that another stream's work still
-// uses is passed over while the library may have more memory, so that independent streams overlap.  At most an eighth of the device's memory is
-// kept (least recently used freed first), and a block that 1024 later returns did not need is freed.
-// Everything kept, and what the pool holds, goes back when any allocation of the library runs out of
-// memory (with_room) and when the program asks for it (release): other allocators of the process, torch's
-// among them, cannot reach it.
+// uses is passed over while the library may have more memory, so that independent streams overlap.  At
+// most an eighth of the device's memory is kept (least recently used freed first), and a block that 1024
+// later returns did not need is freed.  Everything kept, and what the pool holds, goes back when any
+// allocation of the library runs out of memory (with_room) and when the program asks for it (release):
+// other allocators of the process, torch's among them, cannot reach it.
 #pragma once
 
 #include <hip/hip_runtime.h>
