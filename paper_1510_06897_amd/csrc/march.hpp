@@ -11,8 +11,8 @@
 //
 // Why: the direction-split kernels read every spinor eight times and every link twice through L1 and
 // L2.  With vectors beyond the last-level cache the re-reads that miss L2 are what they wait for: K and
-// the fused K step on 64 FP64 vectors of 16^3 x 32 read 5.4 and 9.5 GB from beyond L2 (their bytes: 1.7
-// and 3.3), 4.3 and 7.5 GB here, and take 2.74 ms together instead of 3.65.  Bound by HBM: the 18 right-hand sides of
+// the fused K step on 64 FP64 vectors of 16^3 x 32 read 5.4 and 9.5 GB from beyond L2 (their inputs: 1.7
+// and 4.9), 4.3 and 7.5 GB here, and take 2.74 ms together instead of 3.65.  Bound by HBM: the 18 right-hand sides of
 // 12 x 16^3 x 32 + 4 x 8^3 x 16 + 2 x 12^3 x 24 in FP32 with two-row links move 861 MB in 163 us (5.3
 // TB/s; a plain copy: 4.9), the direction-split pair kernel 813 MB in 184 us: in this case the gain is
 // the rate, not fewer bytes; the degree-299 sign function takes 49.4 instead of 56.0 ms.

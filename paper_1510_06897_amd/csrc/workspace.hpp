@@ -140,10 +140,13 @@ class BlockCache {
  private:
   void keep(Block &b) {
     const int dev = b.dev;
-    {
+    try {
       std::lock_guard<std::mutex> lk(mu_);
       b.stamp = ++clock_;
       free_.push_back(b);
+    } catch (...) {  // no host memory to remember it by
+      drop(b);
+      return;
     }
     b = Block();
     trim(dev, limit(dev));
