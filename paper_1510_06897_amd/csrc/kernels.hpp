@@ -85,9 +85,10 @@ struct StepItem {
   // Right-hand-side groups of the workgroup order: right-hand-side blocks run fastest inside
   // groups of rgroup blocks, then the site blocks, then the groups (0: one group of all).
   int rgroup;
-  // Plan of the t-marching form (march.hpp; ct = 0: not planned): tile Lx x mty x mtz, t slices per
-  // workgroup, right-hand sides per group of its workgroup order, first workgroup.
-  int mty, mtz, ct, mgroup, mblk0;
+  // Plan of the t-marching form (march.hpp; nt = 0: not planned): tile Lx x mty x mtz, t chunks (of
+  // lengths that differ by at most one), right-hand sides per group of its workgroup order, first
+  // workgroup.
+  int mty, mtz, nt, mgroup, mblk0;
 };
 
 // item-local workgroup lb -> (right-hand-side block rb, site block b) for nrb right-hand-side

@@ -107,6 +107,40 @@ inline int march_tile(const Geom &g, int &ty, int &tz) {
   return (int)best;
 }
 
+// Least t slices of a chunk for a launch of `slices` tile slices: the longest of 4, 8, 16, 32 that
+// leaves 2048 workgroups (a chunk re-reads the slices before and after it, so longer is less
+// traffic: 64 FP64 vectors of 16^3 x 32 2.91, 2.78, 2.73 ms at 8, 16, 32; but a launch of few
+// workgroups ends in a nearly empty round: 12 vectors 263, 273, 288 us at 4, 8, 16).
+inline int march_chunk(int64_t slices) {
+  int ct = 4;
+  while (ct < 32 && slices / (2 * ct) >= 2048) ct *= 2;
+  return ct;
+}
+// chunks of Lt slices: the lengths are ct or more, up to 2 ct - 1 (an extent of 5, 6 or 7 is one chunk: 16^3 x 7,
+// 28 FP64 vectors 136 us, in two chunks 175; 16^3 x 6, 32 vectors 124 and 134)
+inline int march_chunks(int lt, int ct) { return lt / ct > 1 ? lt / ct : 1; }
+// Plans the items of a launch (all of them have a tile); returns its workgroups.
+inline int march_plan(StepItem *items, int n) {
+  int64_t slices = 0;
+  for (int i = 0; i < n; ++i) {
+    StepItem &it = items[i];
+    slices += (int64_t)it.g.V / march_tile(it.g, it.mty, it.mtz) * it.nrhs;
+  }
+  const int ct = march_chunk(slices);
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    StepItem &it = items[i];
+    const int tiles = it.g.L[1] / it.mty * (it.g.L[2] / it.mtz);
+    it.nt = march_chunks(it.g.L[3], ct);
+    // the tiles of about 32 workgroups (an XCD's compute units) run side by side, so that faces are
+    // read from its L2
+    it.mgroup = tiles < 32 ? 32 / tiles : 1;
+    it.mblk0 = blocks;
+    blocks += it.nrhs * tiles * it.nt;
+  }
+  return blocks;
+}
+
 // LDS bytes of a workgroup: 12 components of the tile and its faces
 template <class C>
 __host__ __device__ constexpr int march_lds_bytes() {
@@ -139,8 +173,12 @@ __host__ __device__ __forceinline__ MarchPlace march_place(const StepItem &I, co
   const int within = lb - gi * span;
   p.r = gi * gs + within % gl;
   p.tile = within / gl;
-  p.t0 = chunk * I.ct;
-  p.t1 = min(p.t0 + I.ct, ex.lt);
+  // chunk lengths differ by at most one; which chunks are the long ones varies with the tile and the
+  // right-hand side, as an XCD's range of workgroups holds few chunks (16^3 x 33, FP32, 8 chunks, the long
+  // one always last / varying: 11 vectors 163 / 150 us, 21 vectors 296 / 271)
+  const int turn = (p.r + p.tile) % I.nt;
+  p.t0 = (chunk * ex.lt + turn) / I.nt;
+  p.t1 = ((chunk + 1) * ex.lt + turn) / I.nt;
   p.n = ex.lx * ty * tz;
   p.y0 = (p.tile % nty) * ty;
   p.z0 = (p.tile / nty) * tz;

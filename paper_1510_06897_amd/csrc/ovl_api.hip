@@ -302,21 +302,6 @@ bool march_ok(const StepItem *items, int n) {
   return true;
 }
 
-// t slices per workgroup of a launch of `slices` tile slices: the longest of 4, 8, 16, 32 that
-// leaves 2048 workgroups (a chunk re-reads the slices before and after it, so longer is less
-// traffic: 64 FP64 vectors of 16^3 x 32 2.91, 2.78, 2.73 ms at 8, 16, 32; but a launch of few
-// workgroups ends in a nearly empty round: 12 vectors 263, 273, 288 us at 4, 8, 16).
-int march_chunk(int64_t slices) {
-  int ct = 4;
-  while (ct < 32 && slices / (2 * ct) >= 2048) ct *= 2;
-  return ct;
-}
-int64_t march_slices(const StepItem &it) {
-  int ty, tz;
-  const int n = march_tile(it.g, ty, tz);
-  return n ? (int64_t)it.g.V / n * it.nrhs : 0;
-}
-
 // bytes of the three vectors and the links of a launch's steps
 int64_t step_set_bytes(int prec, const StepItem *items, int n) {
   const int link = prec == P_F64 ? 16 : prec == P_F32 ? 8 : 4;
@@ -452,29 +437,14 @@ void plan_launch(StepArgs<TABLE> &p, StepItem *items, int n, const LaunchCfg &cf
     const int grhs = it.rgroup > 0 ? std::min(it.nrhs, it.rgroup * cfg.rb) : it.nrhs;
     if (cfg.tiles == 1 || cfg.tiles == kMarch)
       step_tile(it.g, cfg.spb, site_bytes * grhs, it.ty, it.tz);
-    it.ct = 0;
+    it.nt = 0;
     total += item_blocks(it.g.V, cfg.spb) * ((it.nrhs + cfg.rb - 1) / cfg.rb);
   }
   p.total_blocks = total;
   p.remap = cfg.remap;
   p.march_blocks = 0;
   if (cfg.tiles != kMarch) return;
-  int64_t slices = 0;
-  for (int i = 0; i < n; ++i) slices += march_slices(items[i]);
-  const int ct = march_chunk(slices);
-  int blocks = 0;
-  for (int i = 0; i < n; ++i) {
-    StepItem &it = items[i];
-    march_tile(it.g, it.mty, it.mtz);
-    const int tiles = it.g.L[1] / it.mty * (it.g.L[2] / it.mtz);
-    it.ct = std::min(ct, it.g.L[3]);
-    // the tiles of about 32 workgroups (an XCD's compute units) run side by side, so that faces are
-    // read from its L2
-    it.mgroup = std::max(1, 32 / tiles);
-    it.mblk0 = blocks;
-    blocks += it.nrhs * tiles * ((it.g.L[3] + it.ct - 1) / it.ct);
-  }
-  p.march_blocks = blocks;
+  p.march_blocks = march_plan(items, n);
 }
 
 int site_bytes_of(Prec prec) {

@@ -19,7 +19,7 @@ static Ext4 extents(const Geom &g) {
   return e;
 }
 
-static bool check(const Geom &g, int nrhs, int mgroup, int ct) {
+static bool check(const Geom &g, int nrhs, int mgroup, int nt) {
   StepItem it;
   std::memset(&it, 0, sizeof(it));
   it.g = g;
@@ -27,15 +27,16 @@ static bool check(const Geom &g, int nrhs, int mgroup, int ct) {
   const int n = march_tile(g, it.mty, it.mtz);
   if (!n) return true;
   it.mgroup = mgroup;
-  it.ct = ct;
+  it.nt = nt;
   const Ext4 ex = extents(g);
   const int ntile = g.L[1] / it.mty * (g.L[2] / it.mtz);
-  const int blocks = nrhs * ntile * ((g.L[3] + ct - 1) / ct);
+  const int blocks = nrhs * ntile * nt;
   std::vector<int> seen((size_t)nrhs * ntile * g.L[3], 0);
   for (int lb = 0; lb < blocks; ++lb) {
     const MarchPlace p = march_place(it, ex, lb);
     if (p.r < 0 || p.r >= nrhs || p.tile < 0 || p.tile >= ntile || p.n != n || n > kMarchThreads) return false;
     for (int t = p.t0; t < p.t1; ++t) ++seen[((size_t)p.r * ntile + p.tile) * g.L[3] + t];
+    if (p.t1 <= p.t0 || p.t1 - p.t0 > (g.L[3] + nt - 1) / nt) return false;
     if (p.r || p.t0) continue;  // the staging depends on the tile alone
     std::vector<int> stage(2 * kMarchThreads, -1);
     for (int tid = 0; tid < kMarchThreads; ++tid) {
@@ -60,6 +61,27 @@ static bool check(const Geom &g, int nrhs, int mgroup, int ct) {
   return true;
 }
 
+// slices of the busiest eighth of a planned launch's workgroups (an XCD's range) over the mean
+static double imbalance(const Geom &g, int nrhs) {
+  StepItem it;
+  std::memset(&it, 0, sizeof(it));
+  it.g = g;
+  it.nrhs = nrhs;
+  const int blocks = march_plan(&it, 1);
+  const Ext4 ex = extents(g);
+  double most = 0.0, all = 0.0;
+  for (int x = 0; x < 8; ++x) {
+    double sum = 0.0;
+    for (int lb = blocks * x / 8; lb < blocks * (x + 1) / 8; ++lb) {
+      const MarchPlace p = march_place(it, ex, lb);
+      sum += p.t1 - p.t0;
+    }
+    all += sum;
+    most = sum > most ? sum : most;
+  }
+  return most / (all / 8);
+}
+
 int main() {
   int tiles = 0, more_faces = 0, bad = 0;
   for (int x = 1; x <= 36; ++x)
@@ -80,7 +102,16 @@ int main() {
     bad += !check(g, 1, 1, 1);
   for (int nrhs : {1, 2, 5, 40})
     for (int mgroup : {1, 2, 8, 32})
-      for (int ct : {1, 4, 5}) bad += !check(geom(16, 8, 8, 9), nrhs, mgroup, ct);
+      for (int nt : {1, 2, 4, 5, 9}) bad += !check(geom(16, 8, 8, 9), nrhs, mgroup, nt);
+  // ragged t extents: chunks of two lengths, spread evenly
+  for (int lt : {5, 7, 9, 13, 17, 31, 33, 47})
+    for (int nrhs : {6, 11, 14, 21, 40}) {
+      const double x = imbalance(geom(16, 16, 16, lt), nrhs);
+      if (x > 1.04) {
+        ++bad;
+        std::printf("16^3 x %d, %d vectors: the busiest XCD has %.2f times the mean\n", lt, nrhs, x);
+      }
+    }
   std::printf("%d cross-sections with a tile, %d with more face sites than tile sites, %d wrong\n", tiles,
               more_faces, bad);
   return bad || !tiles || !more_faces;
