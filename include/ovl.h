@@ -404,8 +404,10 @@ int ovl_autotune_load(const char *cache_path);
  * site-right-hand-sides, 16 below 64K, else 64 in tile order, with 128 (two sites per lane) for
  * FP32 links from 512K site-right-hand-sides; with 16-bit links memory order (0) while a step's three
  * vectors and the links are below 120 MB; order 3 with 64 where a tile fits every lattice, at least half
- * of the sites (times right-hand sides) lie in 256-site tiles, and a step's vectors and links reach 256
- * MB; remap on; rb 1.  Two sites per lane need FP32
+ * of the sites (times right-hand sides) lie in 256-site tiles, and the three vectors of a step and the
+ * links reach 256 MB (K and other steps on two vectors: those two; lattices below 12 MB a vector, t
+ * extents that split unevenly and launches of few workgroups need more with FP64 and FP32 links);
+ * remap on; rb 1.  Two sites per lane need FP32
  * spinors, an even Lx and 16-byte aligned vectors (a call whose vectors are not aligned runs
  * with 64); a slab or t-marching entry that does not fit the lattice falls back to the
  * default. */

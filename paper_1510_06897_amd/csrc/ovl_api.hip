@@ -283,6 +283,7 @@ void step_tile(const Geom &g, int spb, int site_bytes, int &ty, int &tz) {
 struct LaunchCfg {
   int spb, tiles, remap, rb;
 };
+constexpr int kMaxBatch = 16;  // items of a launch
 constexpr int kMarch = 3;  // LaunchCfg::tiles of the t-marching form (spb 64, rb 1)
 struct TuneKey {
   int prec;
@@ -302,35 +303,62 @@ bool march_ok(const StepItem *items, int n) {
   return true;
 }
 
-// bytes of the three vectors and the links of a launch's steps
-int64_t step_set_bytes(int prec, const StepItem *items, int n) {
+// bytes of nvec vectors and the links of a launch's steps
+int64_t step_set_bytes(int prec, const StepItem *items, int n, int nvec) {
   const int link = prec == P_F64 ? 16 : prec == P_F32 ? 8 : 4;
   int64_t bytes = 0;
   for (int i = 0; i < n; ++i)
-    bytes += 3 * 12 * (int64_t)items[i].g.V * items[i].nrhs * (prec == P_F64 ? 16 : 8) +
+    bytes += (int64_t)nvec * 12 * items[i].g.V * items[i].nrhs * (prec == P_F64 ? 16 : 8) +
              (int64_t)36 * items[i].g.V * link;
   return bytes;
 }
 
-// Where the t-marching form is the default: the step's three vectors and the links exceed the 256 MB
-// last-level cache, and most sites lie in tiles of kMarchThreads sites.  Measured, one fused step in
-// the default form / t-marching, us: 16^3 x 32 FP64 3 vectors (302 MB with the links) 79.8 / 79.7,
-// 4 110 / 91, 12 341 / 263; FP32 6 vectors (265 MB) 69.7 / 67.2, 8 105 / 96, 12 166 / 142; 16-bit
+// Where the t-marching form is the default: the vectors that the step touches (nvec: three in a recurrence,
+// two in K) and the links reach the 256 MB last-level cache, and most sites lie in tiles of kMarchThreads
+// sites.  Measured, one fused step in the default form / t-marching, us: 16^3 x 32 FP64 3 vectors (302 MB
+// with the links) 79.8 / 79.7, 4 110 / 91, 12 341 / 263; FP32 8 vectors 105 / 96, 12 166 / 142; 16-bit
 // links 4 vectors (170 MB) 43.3 / 38.6, 2 (94 MB) 25.0 / 27.7, 12 169 / 124; 16^3 x 64 FP64 1 vector
 // (302 MB) 64.4 / 54.0.  Below the cache size the form has too few workgroups (8^3 x 16, 12 FP64
 // vectors: 18.8 / 29.0), and 192-site tiles leave a quarter of the threads idle (12^3 x 24, 24 FP32
 // vectors: 93 / 103).
-bool march_pays(int prec, const StepItem *items, int n) {
-  int64_t sites = 0, full = 0;
-  for (int i = 0; i < n; ++i) sites += (int64_t)items[i].g.V * items[i].nrhs;
-  if (step_set_bytes(prec, items, n) < (int64_t)256 << 20) return false;
+// FP64 and FP32 links: at 256 MB this holds for lattices of at least 12 MB a vector in equal chunks of four or
+// more slices (they gain most: the other forms re-read the t neighbours of such lattices from beyond L2;
+// 16^3 x 32 to 16 x 20 x 20 x 40, 3 vectors 288 to 360 MB: 0.99 to 1.27 times as fast).  Smaller lattices,
+// chunks of unequal lengths and t extents below four need more, measured over 31 lattices in steps of two and
+// three vectors as the time of the default form over this one:
+// - three t slices: a shorter lattice's chunk reads more slices before and after it than its own (16^3 x 1,
+//   533 vectors, default / t-marching: FP64 360 / 397, FP32 183 / 219; 16^3 x 2, 266 FP32 vectors 197 / 209);
+// - bytes: FP64 256 MB, 384 MB with unequal chunks (16^3 x 17 0.86 to 0.93 at 267 to 293 MB, 1.16 at 395); FP32
+//   320 and 560 MB (8^3 x 16 0.94 at 263, 1.05 at 311; 8 x 16 x 16 x 13 0.87 to 1.0 up to 504);
+// - up to five rounds of workgroups (one a compute unit in FP64, two in FP32), a last round four fifths full on
+//   average: 16 x 4 x 4 x 8 FP64 1.11 at 285 MB and 2.0 rounds, 0.91 at 310 MB and 2.1 rounds.
+bool march_pays(int prec, const StepItem *items, int n, int nvec) {
+  constexpr int64_t MB = (int64_t)1 << 20;
+  StepItem plan[kMaxBatch];
+  const int64_t bytes = step_set_bytes(prec, items, n, nvec);
+  if (n > kMaxBatch || bytes < 256 * MB) return false;
   for (int i = 0; i < n; ++i) {
     int ty, tz;
-    const int t = march_tile(items[i].g, ty, tz);
-    if (!t) return false;
-    if (t == kMarchThreads) full += (int64_t)items[i].g.V * items[i].nrhs;
+    if (!march_tile(items[i].g, ty, tz)) return false;
+    plan[i] = items[i];
   }
-  return 2 * full >= sites;
+  const int blocks = march_plan(plan, n);
+  int64_t sites = 0, full = 0, even = 0, big = 0;  // all; in whole tiles; in equal chunks; of large lattices
+  for (int i = 0; i < n; ++i) {
+    const Geom &g = items[i].g;
+    const int64_t s = (int64_t)g.V * items[i].nrhs;
+    const bool eq = g.L[3] >= 4 && g.L[3] % plan[i].nt == 0;
+    sites += s;
+    if (g.L[0] * plan[i].mty * plan[i].mtz == kMarchThreads && (g.L[3] >= 3 || prec == P_F32_BF16)) full += s;
+    if (eq) even += s;
+    if (eq && (int64_t)12 * g.V * (prec == P_F64 ? 16 : 8) >= 12 * MB) big += s;
+  }
+  if (2 * full < sites) return false;
+  if (prec == P_F32_BF16 || 2 * big >= sites) return true;
+  const bool eq = 2 * even >= sites;
+  if (bytes < (prec == P_F64 ? (eq ? 256 : 384) : (eq ? 320 : 560)) * MB) return false;
+  const int slots = prec == P_F64 ? 256 : 512, rounds = (blocks + slots - 1) / slots;
+  return rounds > 5 || (int64_t)blocks * 5 > (int64_t)4 * rounds * slots;
 }
 
 // Launch form without a measured one.  16-bit links run in memory order while the step's vectors and
@@ -340,7 +368,7 @@ bool march_pays(int prec, const StepItem *items, int n) {
 // 285 MB 66.1 / 69.0).  FP32 is even there (16^3 x 32 18.6 / 18.5), FP64 faster in tiles (32.6 / 35.5).
 LaunchCfg default_cfg(int64_t work, int prec, const StepItem *items, int n) {
   const int spb = (prec == P_F32 && work >= 512 * 1024) ? 128 : launch_spb(work);
-  const bool tiles = prec != P_F32_BF16 || step_set_bytes(prec, items, n) >= (int64_t)120 << 20;
+  const bool tiles = prec != P_F32_BF16 || step_set_bytes(prec, items, n, 3) >= (int64_t)120 << 20;
   return LaunchCfg{spb, tiles, 1, 1};
 }
 
@@ -355,7 +383,8 @@ TuneKey tune_key(int prec, const StepItem *items, int n) {
   return k;
 }
 
-LaunchCfg lookup_cfg(int prec, const StepItem *items, int n, int64_t work) {
+// nvec: vectors that a step of the launch touches
+LaunchCfg lookup_cfg(int prec, const StepItem *items, int n, int64_t work, int nvec) {
   const TuneKey k = tune_key(prec, items, n);
   std::lock_guard<std::mutex> lk(g_tune_mu);
   auto it = g_tuned.find(k);
@@ -363,7 +392,7 @@ LaunchCfg lookup_cfg(int prec, const StepItem *items, int n, int64_t work) {
     if (it->second.tiles != kMarch || march_ok(items, n)) return it->second;
     return default_cfg(work, prec, items, n);
   }
-  return march_pays(prec, items, n) ? LaunchCfg{64, kMarch, 1, 1} : default_cfg(work, prec, items, n);
+  return march_pays(prec, items, n, nvec) ? LaunchCfg{64, kMarch, 1, 1} : default_cfg(work, prec, items, n);
 }
 
 // two sites per lane need FP32 spinors, an even Lx (pairs never straddle an x line) and 16-byte
@@ -615,11 +644,25 @@ int dispatch_cfg(Prec prec, StepArgs<false> &p, const LaunchCfg &cfg, hipStream_
   plan_launch(p, &p.item, 1, cfg, prec);
   return dispatch_step(prec, p, cfg, s);
 }
+// distinct vectors among a single problem's operands
+int step_vectors(const StepArgs<false> &p) {
+  const StepItem &I = p.item;
+  auto vec = [&](int role) { return role == ROLE_PSI ? I.psi : I.buf[role - 1]; };
+  const void *v[4] = {vec(p.v_role), vec(p.out_role), p.w_role == ROLE_NONE ? nullptr : vec(p.w_role),
+                      p.a != 0.0 ? I.psi : nullptr};
+  int n = 0;
+  for (int i = 0; i < 4; ++i) {
+    bool seen = !v[i];
+    for (int j = 0; j < i; ++j) seen = seen || v[j] == v[i];
+    n += !seen;
+  }
+  return n;
+}
 int dispatch_single(Prec prec, StepArgs<false> &p, hipStream_t s) {
   const int64_t work = items_work(&p.item, 1);
   const bool pairs = pairs_ok(prec, &p.item, 1);
   const LaunchCfg cfg = fit_slab(
-      fit_cfg(lookup_cfg((int)prec, &p.item, 1, work), pairs), p.item, prec,
+      fit_cfg(lookup_cfg((int)prec, &p.item, 1, work, step_vectors(p)), pairs), p.item, prec,
       work, pairs);
   return dispatch_cfg(prec, p, cfg, s);
 }
@@ -757,7 +800,6 @@ struct SignJob {
   int nrhs;
 };
 
-constexpr int kMaxBatch = 16;
 
 // ---------------------------------------------------------------------------------------------
 // Step graphs.  A small single-problem evaluation is bound by the launch rate (its steps take a
@@ -863,7 +905,7 @@ LaunchCfg sign_cfg(const SignJob *jobs, int nj, Prec prec) {
             (!jobs[j].d || aligned16(jobs[j].d->phi_store));
   StepItem key_items[kMaxBatch];
   for (int j = 0; j < nj; ++j) fill_item(key_items[j], jobs[j].g, jobs[j].nrhs);
-  LaunchCfg cfg = fit_cfg(lookup_cfg((int)prec, key_items, nj, work), pairs);
+  LaunchCfg cfg = fit_cfg(lookup_cfg((int)prec, key_items, nj, work, 3), pairs);
   if (TABLE) return cfg.tiles == 2 ? fit_cfg(default_cfg(work, prec, key_items, nj), pairs) : cfg;
   return fit_slab(cfg, key_items[0], prec, work, pairs);
 }
@@ -3119,7 +3161,7 @@ int ovl_launch_config(const ovl_gauge *g, int nrhs, int spin_dt, int cfg_out[3])
   const bool pairs = prec != P_F64 && g->g.L[0] % 2 == 0;
   StepItem it;
   fill_item(it, g, nrhs);
-  const LaunchCfg c = fit_slab(fit_cfg(lookup_cfg((int)prec, &it, 1, work), pairs), it, prec, work, pairs);
+  const LaunchCfg c = fit_slab(fit_cfg(lookup_cfg((int)prec, &it, 1, work, 3), pairs), it, prec, work, pairs);
   cfg_out[0] = c.spb;
   cfg_out[1] = c.tiles;
   cfg_out[2] = c.remap;

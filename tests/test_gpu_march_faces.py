@@ -98,7 +98,7 @@ def test_march_by_default_in_a_batch(ovl, store, other):  # noqa: F811
     p = ovl.Polynomial(och.coeffs_sign_interp(11, 0.1), LMAX)
     gen = torch.Generator(device="cuda").manual_seed(7)
     probs = []
-    for i, (dims, n) in enumerate([((16, 16, 16, 30), 4 if store == "f64" else 8), (other, 2)]):
+    for i, (dims, n) in enumerate([((16, 16, 16, 32), 4 if store == "f64" else 8), (other, 2)]):
         x = torch.randn(n, 4, 3, *reversed(dims), dtype=CDT[store], device="cuda", generator=gen)
         probs.append((ovl.GaugeField(field(dims, 30 + i), store), x))
     assert ovl.batch_launch_config(probs) == (64, 3, 1, 1)
