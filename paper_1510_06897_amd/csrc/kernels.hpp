@@ -1182,7 +1182,7 @@ __global__ void __launch_bounds__(kBlock)
 
 // inout_r += sum_{e0 <= i < e0 + ne} phi_i (w.v[i - e0] * c[r][i]) with the weights passed by value
 // in the kernel arguments (the public correction entry point: nothing to stage on the device).
-// A thread owns one spin-colour component of one site for up to RB right-hand sides: every basis
+// A thread owns E spin-colour components (kBlock apart) for up to RB right-hand sides: every basis
 // element read feeds RB multiply-adds, so the basis is read once per RB right-hand sides; the
 // coefficients w c of the launch sit in LDS.  Bound by memory (24 FP64 vectors added to 12 right-hand
 // sides of 16^3 x 32: 1.21 GB in 264 us, 4.6 TB/s; with the basis read once per right-hand side
@@ -1192,20 +1192,24 @@ constexpr int kWStage = 64;   // of which this many have their coefficients in L
 struct WChunk {
   double v[kWChunk];
 };
-template <class C, class SE, int RB>
+template <class C, class SE, int RB, int E>
 __global__ void __launch_bounds__(kBlock)
     correct_w_kernel(SE *inout, const SE *__restrict__ phi, int e0, int ne, int n_ev, int nrhs,
                      const double2 *__restrict__ c, WChunk w, int64_t n) {
   __shared__ cx<C> d[kWStage][RB];
-  const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;  // element of a vector, n = 12 V
+  const int64_t k0 = (int64_t)blockIdx.x * (kBlock * E) + threadIdx.x;
   const int r0 = blockIdx.y * RB;
   const int nr = min(RB, nrhs - r0);
-  const bool in = k < n;
   SE *io = inout + (int64_t)r0 * n;
-  cx<C> acc[RB];
+  bool in[E];
+  cx<C> acc[E][RB];
 #pragma unroll
-  for (int r = 0; r < RB; ++r)
-    if (r < nr && in) acc[r] = load_c<C>(io, (int64_t)r * n + k);
+  for (int x = 0; x < E; ++x) in[x] = k0 + x * kBlock < n;
+#pragma unroll
+  for (int x = 0; x < E; ++x)
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+      if (r < nr && in[x]) acc[x][r] = load_c<C>(io, (int64_t)r * n + k0 + x * kBlock);
   for (int s0 = 0; s0 < ne; s0 += kWStage) {
     const int ns = min(kWStage, ne - s0);
     __syncthreads();
@@ -1218,19 +1222,27 @@ __global__ void __launch_bounds__(kBlock)
       }
     }
     __syncthreads();
-    if (in) {
 #pragma unroll 4
-      for (int e = 0; e < ns; ++e) {
-        const cx<C> f = load_c<C>(phi, (int64_t)(e0 + s0 + e) * n + k);
+    for (int e = 0; e < ns; ++e) {
+      cx<C> f[E];
 #pragma unroll
-        for (int r = 0; r < RB; ++r)
-          if (r < nr) acc[r] = cmadd(acc[r], f, d[e][r]);
-      }
+      for (int x = 0; x < E; ++x)
+        if (in[x]) f[x] = load_c<C>(phi, (int64_t)(e0 + s0 + e) * n + k0 + x * kBlock);
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+        if (r < nr) {
+          const cx<C> dd = d[e][r];
+#pragma unroll
+          for (int x = 0; x < E; ++x)
+            if (in[x]) acc[x][r] = cmadd(acc[x][r], f[x], dd);
+        }
     }
   }
 #pragma unroll
-  for (int r = 0; r < RB; ++r)
-    if (r < nr && in) store_c(io, (int64_t)r * n + k, acc[r]);
+  for (int x = 0; x < E; ++x)
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+      if (r < nr && in[x]) store_c(io, (int64_t)r * n + k0 + x * kBlock, acc[x][r]);
 }
 
 // v *= 1 / sqrt(nrm2[0].x); records the norm before scaling into norms[slot]

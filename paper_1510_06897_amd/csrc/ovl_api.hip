@@ -2194,17 +2194,25 @@ int ovl_defl_correct(const ovl_defl *d, void *inout, const double *c_dev, const 
     WChunk w;
     for (int k = 0; k < kWChunk; ++k) w.v[k] = k < ne ? w_host[e0 + k] : 0.0;
     const int64_t n = (int64_t)12 * V;
-    auto go = [&](auto kernel, auto *io, const auto *phi, int rb) {
-      const dim3 grid((unsigned)((n + kBlock - 1) / kBlock), (unsigned)((nrhs + rb - 1) / rb));
+    auto go = [&](auto kernel, auto *io, const auto *phi, int rb, int el) {
+      const dim3 grid((unsigned)((n + kBlock * el - 1) / (kBlock * el)), (unsigned)((nrhs + rb - 1) / rb));
       kernel<<<grid, kBlock, 0, s>>>(io, phi, e0, ne, d->n_ev, nrhs, (const double2 *)c_dev, w, n);
     };
-    // right-hand sides per thread: the smallest of 1, 4, 16 that holds them (16 a pass beyond)
+    // Right-hand sides per thread: the smallest of 1, 4, 16 that holds them (16 a pass beyond).  16 need 800
+    // workgroups, else the multiply-adds of a thread are the launch's time: 24 FP64 modes, 16 right-hand
+    // sides at 16 / 4: 256 sites 25 / 11 us, 8^3 x 16 34 / 21 (12 and 28 without passes of right-hand sides).
+    // FP32 components are 8 bytes: two a thread on large lattices, for loads in flight (4 right-hand sides of
+    // 16^3 x 32, 1 mode: 21.7 -> 18.8 us; FP64 components are 16 bytes and gain nothing).
     auto pick = [&](auto zero, auto *io, const auto *phi) {
       using C = decltype(zero);
       using SE = std::remove_reference_t<decltype(*io)>;
-      if (nrhs == 1) go(correct_w_kernel<C, SE, 1>, io, phi, 1);
-      else if (nrhs <= 4) go(correct_w_kernel<C, SE, 4>, io, phi, 4);
-      else go(correct_w_kernel<C, SE, 16>, io, phi, 16);
+      const int64_t blocks = (n + kBlock - 1) / kBlock;
+      const bool two = sizeof(C) == 4 && blocks >= 4096;
+      if (nrhs == 1 && two) go(correct_w_kernel<C, SE, 1, 2>, io, phi, 1, 2);
+      else if (nrhs == 1) go(correct_w_kernel<C, SE, 1, 1>, io, phi, 1, 1);
+      else if (nrhs <= 4 && two) go(correct_w_kernel<C, SE, 4, 2>, io, phi, 4, 2);
+      else if (nrhs <= 4 || blocks * ((nrhs + 15) / 16) < 800) go(correct_w_kernel<C, SE, 4, 1>, io, phi, 4, 1);
+      else go(correct_w_kernel<C, SE, 16, 1>, io, phi, 16, 1);
     };
     if (spin_dt == OVL_F64) pick(0.0, (double2 *)inout, (const double2 *)d->phi_store);
     else pick(0.0f, (float2 *)inout, (const float2 *)d->phi_store);
