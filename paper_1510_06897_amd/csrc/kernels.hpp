@@ -904,10 +904,22 @@ __global__ void __launch_bounds__(kBlock)
   if (f) atomicOr(flags, f);
 }
 
+// sum += x, with what the addition rounds off added to low (Knuth's two-sum)
+__device__ __forceinline__ void carry_add(double &sum, double &low, double x) {
+  const double s = sum + x, v = s - sum;
+  low += (sum - (s - v)) + (x - v);
+  sum = s;
+}
+
 // ---------------------------------------------------------------------------------------------
 // deflation projection, pass 1: partial[b][r][i] = sum over this block's sites of
-// conj(phi_i) . psi_r (12 components), FP64 accumulation, CH eigenvectors per block row
-template <class SE, int CH>
+// conj(phi_i) . psi_r (12 components), FP64 accumulation, CH eigenvectors per block row.  CARRY: a
+// thread's running sums keep what each addition rounds off and add it at the end, for several right-hand
+// sides, whose matrix-core form adds in shorter chains (rms error of a coefficient over 36 problems, in
+// 1e-16: 2.4 against 2.5 on the matrix cores, 3.4 without the carry; 1 to 4 modes).  With more than two modes
+// its loop over components stays rolled: unrolled, the loads of all components take the registers
+// (4 modes, 3 right-hand sides of 16^3 x 32: 59 -> 42 us).  Bound by memory.
+template <class SE, int CH, bool CARRY>
 __global__ void __launch_bounds__(kBlock)
     project_partial_kernel(const SE *__restrict__ phi, int n_ev, const SE *__restrict__ psi,
                            int psi_g5, int V, double2 *__restrict__ partial) {
@@ -916,12 +928,12 @@ __global__ void __launch_bounds__(kBlock)
   const int r = blockIdx.z;
   const int nblk = gridDim.x;
   const int nrhs = gridDim.z;
-  double acc[2 * CH];
+  double acc[2 * CH], low[2 * CH];
 #pragma unroll
-  for (int j = 0; j < 2 * CH; ++j) acc[j] = 0.0;
+  for (int j = 0; j < 2 * CH; ++j) acc[j] = low[j] = 0.0;
   const SE *__restrict__ ps = psi + (int64_t)r * 12 * V;
   for (int site = blockIdx.x * kBlock + threadIdx.x; site < V; site += nblk * kBlock) {
-#pragma unroll
+#pragma unroll(CARRY && CH > 2 ? 1 : 12)
     for (int i = 0; i < 12; ++i) {
       cx<double> x = load_c<double>(ps, (int64_t)i * V + site);
       if (psi_g5 && i >= 6) x = -x;
@@ -929,11 +941,21 @@ __global__ void __launch_bounds__(kBlock)
       for (int j = 0; j < CH; ++j) {
         if (i0 + j < n_ev) {
           const cx<double> f = load_c<double>(phi, ((int64_t)(i0 + j) * 12 + i) * V + site);
-          acc[2 * j] = fma(f.re, x.re, fma(f.im, x.im, acc[2 * j]));
-          acc[2 * j + 1] = fma(f.re, x.im, fma(-f.im, x.re, acc[2 * j + 1]));
+          if constexpr (CARRY) {
+            carry_add(acc[2 * j], low[2 * j], fma(f.re, x.re, f.im * x.im));
+            carry_add(acc[2 * j + 1], low[2 * j + 1], fma(f.re, x.im, -f.im * x.re));
+          } else {
+            acc[2 * j] = fma(f.re, x.re, fma(f.im, x.im, acc[2 * j]));
+            acc[2 * j + 1] = fma(f.re, x.im, fma(-f.im, x.re, acc[2 * j + 1]));
+          }
         }
       }
     }
+  }
+  if constexpr (CARRY) {
+#pragma unroll
+    for (int j = 0; j < 2 * CH; ++j)
+      if (low[j] == low[j]) acc[j] += low[j];  // an infinite sum's remainder is NaN (infinity - infinity)
   }
   block_sum<2 * CH>(acc, lds);
   if (threadIdx.x == 0) {
