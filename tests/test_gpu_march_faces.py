@@ -81,13 +81,16 @@ def test_march_faces_force_twins(ovl, tmp_path, store):  # noqa: F811
 
 
 def field(dims, seed):
-    """Special unitary links made on the GPU."""
+    """Special unitary links made on the GPU: two orthonormal rows and the conjugate of their cross product."""
     gen = torch.Generator(device="cuda").manual_seed(seed)
-    m = torch.randn(4, dims[0] * dims[1] * dims[2] * dims[3], 3, 3, dtype=torch.complex128, device="cuda",
-                    generator=gen)
-    q, _ = torch.linalg.qr(m)
-    q[..., 0] /= torch.linalg.det(q)[..., None]
-    return q.permute(0, 2, 3, 1).reshape(4, 3, 3, *reversed(dims)).contiguous()
+    a, b = torch.randn(2, 4, dims[0] * dims[1] * dims[2] * dims[3], 3, dtype=torch.complex128, device="cuda",
+                       generator=gen)
+    a = a / a.norm(dim=-1, keepdim=True)
+    b = b - a * (a.conj() * b).sum(-1, keepdim=True)
+    b = b / b.norm(dim=-1, keepdim=True)
+    c = torch.stack([a[..., 1] * b[..., 2] - a[..., 2] * b[..., 1], a[..., 2] * b[..., 0] - a[..., 0] * b[..., 2],
+                     a[..., 0] * b[..., 1] - a[..., 1] * b[..., 0]], dim=-1).conj()
+    return torch.stack([a, b, c], dim=-2).permute(0, 2, 3, 1).reshape(4, 3, 3, *reversed(dims)).contiguous()
 
 
 @pytest.mark.parametrize("store,other", [("f64", (12, 14, 16, 4)), ("f32", (16, 10, 10, 6)),
