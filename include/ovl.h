@@ -403,7 +403,8 @@ int ovl_autotune_load(const char *cache_path);
  * order, remap} (see ovl_autotune).  Defaults: 8 sites per workgroup below 4K
  * site-right-hand-sides, 16 below 64K, else 64 in tile order, with 128 (two sites per lane) for
  * FP32 links from 512K site-right-hand-sides; with 16-bit links memory order (0) while a step's three
- * vectors and the links are below 120 MB; order 3 with 64 where a tile fits every lattice, at least half
+ * vectors and the links are below 120 MB and the links, input and output of a t slice within 2.6 MB
+ * (of up to 16 right-hand sides, or 4 of more); order 3 with 64 where a tile fits every lattice, at least half
  * of the sites (times right-hand sides) lie in 256-site tiles, and the three vectors of a step and the
  * links reach 256 MB (K and other steps on two vectors: those two; lattices below 12 MB a vector, t
  * extents that split unevenly and launches of few workgroups need more with FP64 and FP32 links);

@@ -361,14 +361,27 @@ bool march_pays(int prec, const StepItem *items, int n, int nvec) {
   return rounds > 5 || (int64_t)blocks * 5 > (int64_t)4 * rounds * slots;
 }
 
+// Right-hand sides whose workgroups for a site block run side by side: up to 16, else groups of kRhsGroup
+// (rhs_group_blocks).
+constexpr int kRhsGroup = 4;
+int rhs_together(int nrhs) { return nrhs <= 16 ? nrhs : kRhsGroup; }
+
 // Launch form without a measured one.  16-bit links run in memory order while the step's vectors and
-// links fit the last-level cache with room: the tiles save L2 misses that cost little there and lose
-// on their shorter XCD ranges (tiles / memory order, us per step: 16^3 x 32 57 MB 15.8 / 15.0, 2 vectors
-// 94 MB 27.5 / 25.9, 20^3 x 32 110 MB 28.1 / 26.5; 16^3 x 32 3 vectors 132 MB 35.5 / 36.3, 24^3 x 48
-// 285 MB 66.1 / 69.0).  FP32 is even there (16^3 x 32 18.6 / 18.5), FP64 faster in tiles (32.6 / 35.5).
+// links fit the last-level cache with room (120 MB) and what lies between a site and its t neighbour, the
+// links, input and output of a t slice, fits an XCD's 4 MB L2 with room (2.6 MB): the tiles save L2 misses
+// that cost little there and lose on their shorter XCD ranges (tiles / memory order, us per step: 16^3 x 32,
+// slices of 1.3 MB, 16.3 / 14.9; 8 x 16^2 x 32 10.4 / 9.3; 20^3 x 32, 2.6 MB, 28.2 / 26.6; with larger slices
+// 24^2 x 16 x 20, 3.0 MB, 20.5 / 21.4; 24^3 x 20, 4.4 MB, 27.1 / 29.6; 32^2 x 16^2, 5.3 MB, 26.7 / 29.3;
+// larger sets: 16^3 x 32 3 vectors 132 MB 35.5 / 36.3, 24^3 x 48 285 MB 66.1 / 69.0).  FP32 is even there
+// (16^3 x 32 18.6 / 18.5), FP64 faster in tiles (32.6 / 35.5).
 LaunchCfg default_cfg(int64_t work, int prec, const StepItem *items, int n) {
   const int spb = (prec == P_F32 && work >= 512 * 1024) ? 128 : launch_spb(work);
-  const bool tiles = prec != P_F32_BF16 || step_set_bytes(prec, items, n, 3) >= (int64_t)120 << 20;
+  bool tiles = prec != P_F32_BF16 || step_set_bytes(prec, items, n, 3) >= (int64_t)120 << 20;
+  for (int i = 0; i < n; ++i) {
+    const Geom &g = items[i].g;
+    const int64_t slice = (int64_t)g.L[0] * g.L[1] * g.L[2] * (36 * 4 + 2 * 96 * rhs_together(items[i].nrhs));
+    tiles = tiles || slice * 10 > (int64_t)26 << 20;
+  }
   return LaunchCfg{spb, tiles, 1, 1};
 }
 
@@ -443,7 +456,6 @@ LaunchCfg fit_slab(LaunchCfg c, const StepItem &it, Prec prec, int64_t work, boo
 // groups of kRhsGroup, so that between a site and its t neighbour only one group's spinors pass
 // through L2 (K on 128 FP64 vectors of 16^3 x 32 in the default configuration: 4.38 ms as one
 // group, 3.63 / 3.57 / 3.54 / 3.63 ms in groups of 1 / 2 / 4 / 8).
-constexpr int kRhsGroup = 4;
 int rhs_group_blocks(int nrhs, int rb) {
   return nrhs <= 16 ? 0 : std::max(1, kRhsGroup / rb);
 }
