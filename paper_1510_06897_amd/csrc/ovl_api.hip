@@ -744,14 +744,14 @@ int project_mfma(const SE *phi, int n_ev, const SE *psi, int psi_g5, int nrhs, i
 // FP64 storage: one right-hand side takes the VALU kernel with FP64 products (each basis vector is
 // read once whatever the kernel), and so do several on a few modes of a larger lattice, where its more
 // numerous workgroups count for more than a basis read once per right-hand side (VALU / matrix cores, us:
-// 16^3 x 32, 1 mode, 2 right-hand sides 25 / 71, 12 sides 44 / 80, 4 modes and 4 sides 50 / 75, 6 and 2
-// 54 / 75; 24^3 x 48, 2 modes and 2 sides 123 / 311; 12^3 x 16, 1 mode, 12 sides 24 / 40, but 5 modes and 2
-// sides 36 / 28; 16 x 24^2 x 32, 3 modes and 6 sides 192 / 153, 8 and 2 188 / 161).
+// 16^3 x 32, 1 mode, 2 right-hand sides 25 / 71, 12 sides 69 / 125, 4 modes and 4 sides 50 / 75, 6 and 2
+// 54 / 75; 24^3 x 48, 2 modes and 2 sides 123 / 311; 12^3 x 16, 1 mode, 12 sides 24 / 40, 4 sides 25 / 25, but 5
+// modes and 2 sides 36 / 28; 16 x 24^2 x 32, 3 modes and 6 sides 192 / 153, 8 and 2 188 / 161).
 // The others take the FP64 matrix cores, where one read of the basis serves 16 right-hand sides
 // and one read of a right-hand side 32 vectors.
 int project(const double2 *phi, int n_ev, const double2 *psi, int psi_g5, int nrhs, int V,
             double2 *partial, int nblk, double2 *c, hipStream_t s) {
-  const bool few = n_ev == 1 ? V >= 16384
+  const bool few = n_ev == 1 ? (int64_t)V * nrhs >= 128 * 1024
                              : V >= 49152 && ((n_ev <= 4 && nrhs <= 4) || (n_ev <= 6 && n_ev * nrhs <= 12));
   if (nrhs > 1 && !few) return project_mfma(phi, n_ev, psi, psi_g5, nrhs, V, partial, nblk, c, s);
   nblk = std::min(nblk, project_blocks_valu(V));

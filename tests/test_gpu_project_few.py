@@ -13,8 +13,9 @@ from tests.test_gpu_parity import ovl  # noqa: F401
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-SITES = {1: ((13, 11, 7, 16), (13, 12, 7, 16))}  # 16016 and 17472 sites with one mode
-MORE = ((13, 12, 16, 19), (13, 12, 17, 19))      # 47424 and 50388 with more
+# small and large lattice by (modes, right-hand sides): 2 and 12 sides of one mode, the others
+SITES = {(1, 2): ((13, 12, 20, 21), (13, 12, 21, 21)), (1, 12): ((13, 12, 7, 9), (13, 12, 7, 11))}
+MORE = ((13, 12, 16, 19), (13, 12, 17, 19))
 
 
 def problem(ovl, dims, n_ev, nrhs):  # noqa: F811
@@ -32,7 +33,7 @@ def problem(ovl, dims, n_ev, nrhs):  # noqa: F811
 @pytest.mark.parametrize("large", [False, True])
 @pytest.mark.parametrize("n_ev,nrhs", [(1, 2), (1, 12), (2, 6), (2, 7), (3, 4), (4, 4), (4, 5), (5, 2), (6, 2), (6, 3)])
 def test_few_modes(ovl, large, n_ev, nrhs):  # noqa: F811
-    dims = SITES.get(n_ev, MORE)[large]
+    dims = SITES.get((n_ev, nrhs), MORE)[large]
     d, phi, x = problem(ovl, dims, n_ev, nrhs)
     got = ovl.defl_project(d, x).cpu().numpy()
     xs = x.cpu().numpy().reshape(nrhs, -1)
@@ -44,7 +45,7 @@ def test_few_modes(ovl, large, n_ev, nrhs):  # noqa: F811
 
 @pytest.mark.parametrize("n_ev", [1, 3, 6])
 def test_nonfinite_entries(ovl, n_ev):  # noqa: F811
-    dims = SITES.get(n_ev, MORE)[1]
+    dims = SITES.get((n_ev, 2), MORE)[1]
     d, _, x = problem(ovl, dims, n_ev, 2)
     want = ovl.defl_project(d, x)
     y = torch.cat([x[:1], x[:1]])
